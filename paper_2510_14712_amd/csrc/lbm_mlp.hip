@@ -192,8 +192,9 @@ __global__ void __launch_bounds__(MLP_BLOCK) k_fields_mlp(Grid g, Phys<float> ph
         Pr = (float)q.P;
         c2 = (float)q.cs2;
         if (counters) {
-            wave_count(&counters[2], active ? (unsigned)it : 0u);
-            wave_count(&counters[3], active ? 1u : 0u);
+            unsigned long long *slot = counter_slot(counters);
+            wave_count(&slot[2], active ? (unsigned)it : 0u);
+            wave_count(&slot[3], active ? 1u : 0u);
         }
     } else {
     float r = fabsf(ph.cv * T - ph.a * rho - e) / (ph.cv * fabsf(T));
@@ -213,8 +214,9 @@ __global__ void __launch_bounds__(MLP_BLOCK) k_fields_mlp(Grid g, Phys<float> ph
     unsigned long long nfb = __popcll(__ballot(fb && active));
     unsigned long long nact = __popcll(__ballot(active));
     if ((tid & 63) == 0 && counters) {
-        atomicAdd(&counters[0], nfb);
-        atomicAdd(&counters[1], nact);
+        unsigned long long *slot = counter_slot(counters);
+        atomicAdd(&slot[0], nfb);
+        atomicAdd(&slot[1], nact);
     }
     if (!active) return;
     float theta = Pr * inv_rho;
@@ -697,13 +699,15 @@ int lbm_mlp_set(lbm_ctx *c, const float *host_params, const float *host_norm) {
 
 int lbm_eos_stats(lbm_ctx *c, double *frac, double *iters) {
     if (!c) return LBM_EINVAL;
-    unsigned long long h[4];
-    if (hipMemcpyAsync(h, c->mlp_counters, sizeof(h), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+    unsigned long long all[COUNTER_SLOTS * COUNTER_STRIDE], h[4] = {0, 0, 0, 0};
+    if (hipMemcpyAsync(all, c->mlp_counters, sizeof(all), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess)
         return LBM_EDEVICE;
+    for (int s = 0; s < COUNTER_SLOTS; s++)
+        for (int k = 0; k < 4; k++) h[k] += all[s * COUNTER_STRIDE + k];
     if (frac) *frac = h[1] ? (double)h[0] / (double)h[1] : 0.0;
     if (iters) *iters = h[3] ? (double)h[2] / (double)h[3] : 0.0;
-    if (hipMemsetAsync(c->mlp_counters, 0, sizeof(h), c->stream) != hipSuccess) return LBM_EDEVICE;
+    if (hipMemsetAsync(c->mlp_counters, 0, sizeof(all), c->stream) != hipSuccess) return LBM_EDEVICE;
     return LBM_OK;
 }
 

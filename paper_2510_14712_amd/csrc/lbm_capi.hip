@@ -196,6 +196,12 @@ __global__ void __launch_bounds__(256) k_probe_copy(const u32x4 *__restrict__ sr
 // ---------------------------------------------------------------------------
 // host helpers
 // ---------------------------------------------------------------------------
+// the flat grid of flat_cell()
+static dim3 flat_grid(const lbm_ctx *c) {
+    const long long plane = (long long)c->p.nx * c->p.ny;
+    return dim3((unsigned)((plane + BX - 1) / BX), (unsigned)c->p.nz);
+}
+
 static dim3 cell_grid(const lbm_ctx *c) {
     return dim3((unsigned)((c->p.nx + BX - 1) / BX), (unsigned)c->p.ny, (unsigned)c->p.nz);
 }
@@ -484,8 +490,8 @@ template <int D, class S> struct Impl {
     static int fields_pass(lbm_ctx *c, bool count = false) {
         Fields<C> fl = get_fields<C>(c);
         dim3 gr = cell_grid(c);
-        hipLaunchKernelGGL((k_moments<D, S>), gr, dim3(BX), 0, c->stream, c->grid, c->ref, (const T *)c->f[c->cur],
-                           (const T *)c->g[c->cur], fl, c->pulled);
+        hipLaunchKernelGGL((k_moments<D, S>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, c->ref,
+                           (const T *)c->f[c->cur], fl, c->pulled);
         hipLaunchKernelGGL((k_lap<D, C>), gr, dim3(BX), 0, c->stream, c->grid, fl);
         if (lbm_eos_uses_mlp(c->p.eos)) {
             int rc = launch_fields_mlp<D, C>(c, fl, count);
@@ -523,17 +529,23 @@ template <int D, class S> struct Impl {
         *fS = fl.sc[src];
         *fs = fl.sc[src + 1];
     }
-    // collide and stream into buffer nxt (multi-kernel path), then what the
-    // wall ghosts emit
+    // collide into buffer nxt (multi-kernel path): the post-collision set, or
+    // with x walls the arrived one and then what the wall ghosts emit
     static void collide_launch(lbm_ctx *c, Fields<C> fl, const C *fS, const C *fs, int nxt) {
         Walls w;
         for (int s = 0; s < 2; s++) {
             for (int a = 0; a < 3; a++) w.u[s][a] = c->p.wall_u[s][a];
             w.T[s] = c->p.wall_T[s];
         }
-        hipLaunchKernelGGL((k_collide<D, S>), cell_grid(c), dim3(BX), 0, c->stream, c->grid, make_phys<C>(c->p),
-                           c->ref, (const T *)c->f[c->cur], (const T *)c->g[c->cur], fl, (T *)c->f[nxt],
-                           (T *)c->g[nxt], fS, fs, w, (C *)c->ghost);
+        if (c->grid.wallx)
+            hipLaunchKernelGGL((k_collide<D, S, true>), flat_grid(c), dim3(BX), 0, c->stream, c->grid,
+                               make_phys<C>(c->p), c->ref, (const T *)c->f[c->cur], fl, (T *)c->f[nxt], fS, fs, w,
+                               (C *)c->ghost, c->pulled);
+        else
+            hipLaunchKernelGGL((k_collide<D, S, false>), flat_grid(c), dim3(BX), 0, c->stream, c->grid,
+                               make_phys<C>(c->p), c->ref, (const T *)c->f[c->cur], fl, (T *)c->f[nxt], fS, fs, w,
+                               (C *)c->ghost, c->pulled);
+        c->pulled = c->grid.wallx ? 0 : 1;
         if (c->grid.wallx)
             hipLaunchKernelGGL((k_wall_emit<D, S>), dim3((unsigned)((c->p.ny + 63) / 64), (unsigned)c->p.nz, 2u),
                                dim3(64), 0, c->stream, c->grid, make_phys<C>(c->p), c->ref, w, fl,
@@ -606,8 +618,8 @@ template <int D, class S> struct Impl {
         int rc = LBM_OK;
         for (int s = 0; s < n && rc == LBM_OK; s++) {
             (void)hipEventRecord(ev[0], c->stream);
-            hipLaunchKernelGGL((k_moments<D, S>), gr, dim3(BX), 0, c->stream, c->grid, c->ref,
-                               (const T *)c->f[c->cur], (const T *)c->g[c->cur], fl, 0);
+            hipLaunchKernelGGL((k_moments<D, S>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, c->ref,
+                               (const T *)c->f[c->cur], fl, c->pulled);
             (void)hipEventRecord(ev[1], c->stream);
             hipLaunchKernelGGL((k_lap<D, C>), gr, dim3(BX), 0, c->stream, c->grid, fl);
             (void)hipEventRecord(ev[2], c->stream);
@@ -848,10 +860,11 @@ int lbm_create(const lbm_params *params, lbm_ctx **out) {
     int cb = params->storage == LBM_STORE_F64 ? 8 : 4;
     make_ref(*params, c->D, c->ref);
     size_t pop_bytes = (size_t)c->Q * N * sb;
-    // field arrays: rho, J[D], G, lap, u[D], F[D], Lam[D], T, P, h, cs2, and
-    // the four shock-capturing work arrays when that scheme is on
+    // field arrays: rho, J[D], G, lap, u[D], F[D], Lam[D], T, P, h, cs2, with
+    // Peng-Robinson e(rho, T), and the four shock-capturing work arrays when
+    // that scheme is on
     c->sc = params->sc_cmu > 0 || params->sc_ceta > 0 || params->sc_ck > 0;
-    size_t nfield = (size_t)(8 + 4 * c->D + (c->sc ? 4 : 0));
+    size_t nfield = (size_t)(8 + 4 * c->D + (lbm_eos_is_pr(params->eos) ? 1 : 0) + (c->sc ? 4 : 0));
     size_t field_bytes = nfield * N * cb;
     // the single-pass step covers periodic z (and every D = 2 lattice)
     // with the van der Waals equation of state, without shock capturing

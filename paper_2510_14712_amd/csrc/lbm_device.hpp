@@ -161,6 +161,18 @@ template <int Q> __host__ __device__ __forceinline__ long long pop_index(const G
     return 2 * ((z * Q + i) * ((long long)g.nx * g.ny) + xy);
 }
 
+// the (f, g) pair of a direction in one access: element index j of f is even
+// and the buffers start at 2 MiB boundaries, so a pair is aligned to its size
+template <class T> struct alignas(2 * sizeof(T)) PopPair {
+    T f, g;
+};
+template <class T> __device__ __forceinline__ PopPair<T> load_pair(const T *p, long long j) {
+    return *reinterpret_cast<const PopPair<T> *>(p + j);
+}
+template <class T> __device__ __forceinline__ void store_pair(T *p, long long j, T f, T g) {
+    *reinterpret_cast<PopPair<T> *>(p + j) = PopPair<T>{f, g};
+}
+
 // Stored population sets come in two forms.  After initialisation (and after
 // lbm_set_populations) the set holds the arrived populations f_i(x) that the
 // next collision uses in place.  The fused step stores the post-collision set

@@ -51,6 +51,10 @@ struct lbm_ctx {
     int ntx = 0, nty = 0, nseg = 1, nlay = 0, chunk = 0;
 };
 
+// equation-of-state modes
+inline bool lbm_eos_is_pr(int eos) { return eos == LBM_EOS_PR || eos == LBM_EOS_PR_PREV || eos == LBM_EOS_PR_MLP; }
+inline bool lbm_eos_uses_mlp(int eos) { return eos == LBM_EOS_MLP || eos == LBM_EOS_PR_MLP; }
+
 // carve the field arrays out of the work buffer
 template <class C> static inline lbm::Fields<C> get_fields(lbm_ctx *c) {
     const long long N = c->grid.N;
@@ -68,6 +72,8 @@ template <class C> static inline lbm::Fields<C> get_fields(lbm_ctx *c) {
     fl.P = w; w += N;
     fl.h = w; w += N;
     fl.cs2 = w; w += N;
+    fl.e = lbm_eos_is_pr(c->p.eos) ? w : nullptr;
+    if (fl.e) w += N;
     for (int k = 0; k < 4; k++) {
         fl.sc[k] = c->sc ? w : nullptr;
         if (c->sc) w += N;
@@ -81,7 +87,3 @@ int lbm_note(hipError_t e);
 // surrogate-EOS variant of the per-cell fields pass (defined with the MLP
 // code); count: add Newton iterations to the context's counters
 template <int D, class C> int launch_fields_mlp(lbm_ctx *c, lbm::Fields<C> fl, bool count);
-
-// equation-of-state modes
-inline bool lbm_eos_is_pr(int eos) { return eos == LBM_EOS_PR || eos == LBM_EOS_PR_PREV || eos == LBM_EOS_PR_MLP; }
-inline bool lbm_eos_uses_mlp(int eos) { return eos == LBM_EOS_MLP || eos == LBM_EOS_PR_MLP; }

@@ -2,14 +2,14 @@
 // Section 3.2 and its flowchart).  Structure-of-arrays populations, x fastest;
 // one thread per cell, grid (ceil(nx / BX), ny, nz).
 //
-// The stored state is the post-streaming population set at time t (what the
-// flowchart initialises to the equilibria).  One step is four launches:
+// One step is four launches:
 //   k_moments  rho, j = sum c_i f_i, G = sum g_i per cell           (eqs. def_h..)
 //   k_lap      discrete Laplacian of rho                             (eq. FK)
 //   k_fields   Korteweg force, u, E, T, P, h, c_s^2, Lambda per cell (eqs. FK,
 //              def_u, def_E, lbm_temp, Pvdw, enthalpy, correction)
-//   k_collide  gradients, shifts, attractors, relax, then stream by pushing
-//              f'_i(x) to x + c_i of the other buffer
+//   k_collide  gradients, shifts, attractors, relax; the next step streams the
+//              post-collision set on the way in (with x walls, the set is
+//              pushed to x + c_i instead)
 //              (eqs. fLBGK, gLBGK, LBMeq, LBMstar, LBMeqG, LBMgstar, sh_*, qc_1)
 #pragma once
 
@@ -25,11 +25,23 @@ template <class C> struct Fields {
     C *lap;              // Laplacian of rho
     C *u, *F, *Lam;      // D components each
     C *T, *P, *h, *cs2;  // scalars
+    C *e;                // Peng-Robinson: e(rho, T) (null for van der Waals)
     C *sc[4];            // shock-capturing work arrays (null when off)
 };
 
 template <int D> __device__ __forceinline__ long long cell_index(const Grid &g, int x, int y, int z) {
     return (long long)x + (long long)g.nx * ((long long)y + (long long)g.ny * z);
+}
+
+// Cell of a thread of the flat grid (ceil(nx ny / BX), nz): the cells of a
+// plane in a row, so that a plane whose rows are shorter than the block, or no
+// multiple of it, still fills its wavefronts.  False beyond the plane.
+__device__ __forceinline__ bool flat_cell(const Grid &g, int &x, int &y, int &z) {
+    const unsigned p = blockIdx.x * (unsigned)BX + threadIdx.x, nx = (unsigned)g.nx;
+    z = blockIdx.y;
+    y = (int)(p / nx);
+    x = (int)(p - (unsigned)y * nx);
+    return y < g.ny;
 }
 
 // neighbour of (x, y, z) shifted by s along axis a (|s| <= 1)
@@ -38,23 +50,6 @@ template <int D> __device__ __forceinline__ long long nb_axis(const Grid &g, int
     else if (a == 1) y = wrap1(y + s, g.ny, g.clampy);
     else z = wrap1(z + s, g.nz, g.clampz);
     return cell_index<D>(g, x, y, z);
-}
-
-// Streaming destinations along one axis of a population leaving coordinate
-// v with velocity component c.  Periodic: wrap(v + c).  Zero-gradient: v + c
-// when inside, and also v itself when v is the boundary cell and c points
-// inward (the cell outside the wall is the boundary cell's own copy).  Returns
-// the number of destinations (0, 1 or 2) written to d[].
-__device__ __forceinline__ int push_axis(int v, int c, int n, int clamp, int d[2]) {
-    int k = 0;
-    int p = v + c;
-    if (!clamp) {
-        d[k++] = p < 0 ? p + n : (p >= n ? p - n : p);
-        return k;
-    }
-    if (p >= 0 && p < n) d[k++] = p;
-    if ((v == 0 && c == 1) || (v == n - 1 && c == -1)) d[k++] = v;
-    return k;
 }
 
 // ---------------------------------------------------------------------------
@@ -126,25 +121,25 @@ __global__ void __launch_bounds__(BX) k_init(Grid g, Phys<double> ph, RefPops re
 }
 
 // ---------------------------------------------------------------------------
+// Bound by HBM: Q pairs read per cell, one access each.
 template <int D, class S>
 __global__ void __launch_bounds__(BX) k_moments(Grid g, RefPops ref, const typename S::T *__restrict__ fi,
-                                                const typename S::T *__restrict__ gi, Fields<typename S::C> fl,
-                                                int pull) {
+                                                Fields<typename S::C> fl, int pull) {
     using C = typename S::C;
     constexpr int Q = Lattice<D>::Q;
-    int x = blockIdx.x * BX + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-    if (x >= g.nx) return;
+    int x, y, z;
+    if (!flat_cell(g, x, y, z)) return;
     long long c = cell_index<D>(g, x, y, z);
     C rho = 0, J[3] = {0, 0, 0}, G = 0;
 #pragma unroll
     for (int i = 0; i < Q; i++) {
-        const long long pi = arrived_index<D>(g, i, x, y, z, pull);
-        C f = S::load(fi, pi, (C)ref.f[i]);
+        const PopPair<typename S::T> pr = load_pair(fi, arrived_index<D>(g, i, x, y, z, pull));
+        C f = S::load(&pr.f, 0, (C)ref.f[i]);
         rho += f;
         if (cx_of(i)) J[0] += cx_of(i) > 0 ? f : -f;
         if (cy_of(i)) J[1] += cy_of(i) > 0 ? f : -f;
         if (D == 3 && cz_of(i)) J[2] += cz_of(i) > 0 ? f : -f;
-        G += S::load(gi, pi, (C)ref.g[i]);
+        G += S::load(&pr.g, 0, (C)ref.g[i]);
     }
     fl.rho[c] = rho;
     for (int a = 0; a < D; a++) fl.J[a * g.N + c] = J[a];
@@ -203,6 +198,7 @@ __global__ void __launch_bounds__(BX) k_fields(Grid g, Phys<C> ph, Fields<C> fl,
         const double Td = pr_temperature(ph, (double)rho, (double)e, warm ? (double)fl.T[c] : 0.0, it);
         const EosPoint q = pr_eos(ph, (double)rho, Td);
         T = (C)Td;
+        fl.e[c] = (C)pr_eos(ph, (double)rho, (double)T).e;
         P = (C)q.P;
         cs2 = (C)q.cs2;
         if (counters) {
@@ -401,20 +397,26 @@ __global__ void __launch_bounds__(64) k_wall_emit(Grid g, Phys<typename S::C> ph
 
 // ---------------------------------------------------------------------------
 // fS, fs: filtered |grad^4 S| and |grad^4 |grad s|| of the shock-capturing
-// passes, or null without shock capturing; w, gb: wall states and ghost
-// buffer (used when g.wallx)
-template <int D, class S>
+// passes, or null without shock capturing.  The arrived populations are read
+// as (f, g) pairs in the form `pull` says and the post-collision pairs stored
+// at the cell itself (aligned rows; the next step streams them on the way in).
+// With x walls (WALL; w: wall states, gb: ghost buffer) the set is pushed to
+// x + c_i instead, since what a wall ghost emits has no place of its own in the
+// post-collision set.  Bound by HBM: 2 Q pairs and about 30 field values per
+// cell.  With f and g apart and every set pushed it took 433 us at 128^3 cells
+// (Peng-Robinson, FP32) and 613 us at 192 x 128^2 (shock capturing); so 246
+// and 372 us.
+template <int D, class S, bool WALL>
 __global__ void __launch_bounds__(BX) k_collide(Grid g, Phys<typename S::C> ph, RefPops ref,
-                                                const typename S::T *__restrict__ fi,
-                                                const typename S::T *__restrict__ gi, Fields<typename S::C> fl,
-                                                typename S::T *__restrict__ fo, typename S::T *__restrict__ go,
+                                                const typename S::T *__restrict__ fi, Fields<typename S::C> fl,
+                                                typename S::T *__restrict__ fo,
                                                 const typename S::C *__restrict__ fS,
                                                 const typename S::C *__restrict__ fs, Walls w,
-                                                typename S::C *__restrict__ gb) {
+                                                typename S::C *__restrict__ gb, int pull) {
     using C = typename S::C;
     constexpr int Q = Lattice<D>::Q;
-    int x = blockIdx.x * BX + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-    if (x >= g.nx) return;
+    int x, y, z;
+    if (!flat_cell(g, x, y, z)) return;
     const long long N = g.N;
     long long c = cell_index<D>(g, x, y, z);
     C rho = fl.rho[c], P = fl.P[c], T = fl.T[c];
@@ -441,7 +443,7 @@ __global__ void __launch_bounds__(BX) k_collide(Grid g, Phys<typename S::C> ph, 
         // neighbours', or a wall ghost's
         C nu[2] = {fl.u[a * N + cm], fl.u[a * N + cp]}, nh[2] = {fl.h[cm], fl.h[cp]};
         C nT[2] = {fl.T[cm], fl.T[cp]}, nL[2] = {fl.Lam[a * N + cm], fl.Lam[a * N + cp]};
-        if (a == 0 && g.wallx) {
+        if (WALL && a == 0) {
             for (int k = 0; k < 2; k++) {
                 if (!(k == 0 ? x == 0 : x == g.nx - 1)) continue;
                 const WallGhost<C> gs = wall_ghost(ph, w, k, rho);
@@ -468,10 +470,12 @@ __global__ void __launch_bounds__(BX) k_collide(Grid g, Phys<typename S::C> ph, 
     C thetas = theta + alpha * theta * divu;                   // eq. sh_temp_1
     C e, es;
     if (ph.pr) {
-        // e(rho, T) by the caloric relation; e(rho, T*) as the energy the
-        // shift of eq. sh_T_1 stands for, e - |F|^2 / (2 rho^2) (exact for an
-        // energy linear in T, and keeps the collision's energy change u . F)
-        e = (C)pr_eos(ph, (double)rho, (double)T).e;
+        // e(rho, T) by the caloric relation, evaluated where the logarithm of
+        // its departure term is at hand (the fields pass); e(rho, T*) as the
+        // energy the shift of eq. sh_T_1 stands for, e - |F|^2 / (2 rho^2)
+        // (exact for an energy linear in T, and keeps the collision's energy
+        // change u . F)
+        e = fl.e[c];
         es = e - FF * inv_rho * inv_rho * C(0.5);
     } else {
         C Ts = T - FF * inv_rho * inv_rho * C(0.5) * ph.inv_cv;  // eq. sh_T_1
@@ -519,36 +523,23 @@ __global__ void __launch_bounds__(BX) k_collide(Grid g, Phys<typename S::C> ph, 
             C cq = ix ? (ix > 0 ? qc[0] : -qc[0]) : (iy ? (iy > 0 ? qc[1] : -qc[1]) : (iz > 0 ? qc[2] : -qc[2]));
             gst += C(0.5) * cq;
         }
-        const long long pi = pop_index<Q>(g, i, z, x + (long long)g.nx * y);
-        C f = S::load(fi, pi, (C)ref.f[i]);
-        C gg = S::load(gi, pi, (C)ref.g[i]);
+        const PopPair<typename S::T> in = load_pair(fi, arrived_index<D>(g, i, x, y, z, pull));
+        C f = S::load(&in.f, 0, (C)ref.f[i]);
+        C gg = S::load(&in.g, 0, (C)ref.g[i]);
         // eqs. fLBGK, gLBGK: f + 2 beta (f^eq - f) + (1 - beta)(f* - f^eq)
         C fn = w_keep * f + w_eq * feq + w_st * fst;
         C gn = w_keep * gg + w_eq * geq + w_st * gst;
         typename S::T fe = S::enc(fn, (C)ref.f[i]), ge = S::enc(gn, (C)ref.g[i]);
-        int dx[2], dy[2], dz[2] = {0, 0};
-        int nxd;
-        if (g.wallx) {
-            // walls: a population leaving through one goes to its ghost
-            const int xd = x + ix;
-            nxd = (xd >= 0 && xd < g.nx) ? 1 : 0;
-            dx[0] = xd;
-            if (!nxd) {
-                const int yg = wrap1(y + iy, g.ny, 0), zg = D == 3 ? wrap1(z + iz, g.nz, 0) : 0;
-                gb[((size_t)(xd < 0 ? 0 : 1) * g.ny * g.nz + (size_t)zg * g.ny + yg) * Q + i] = fn;
-            }
+        if constexpr (WALL) {
+            // periodic in y, z; a population leaving through a wall goes to its ghost
+            const int xd = x + ix, yd = wrap1(y + iy, g.ny, 0), zd = D == 3 ? wrap1(z + iz, g.nz, 0) : 0;
+            if (xd < 0 || xd >= g.nx)
+                gb[((size_t)(xd < 0 ? 0 : 1) * g.ny * g.nz + (size_t)zd * g.ny + yd) * Q + i] = fn;
+            else
+                store_pair(fo, pop_index<Q>(g, i, zd, xd + (long long)g.nx * yd), fe, ge);
         } else {
-            nxd = push_axis(x, ix, g.nx, g.clampx, dx);
+            store_pair(fo, pop_index<Q>(g, i, z, x + (long long)g.nx * y), fe, ge);
         }
-        int nyd = push_axis(y, iy, g.ny, g.clampy, dy);
-        int nzd = D == 3 ? push_axis(z, iz, g.nz, g.clampz, dz) : 1;
-        for (int a = 0; a < nxd; a++)
-            for (int b = 0; b < nyd; b++)
-                for (int cc = 0; cc < nzd; cc++) {
-                    const long long d = pop_index<Q>(g, i, dz[cc], dx[a] + (long long)g.nx * dy[b]);
-                    fo[d] = fe;
-                    go[d] = ge;
-                }
     }
 }
 

@@ -189,6 +189,7 @@ __global__ void __launch_bounds__(MLP_BLOCK) k_fields_mlp(Grid g, Phys<float> ph
             q = pr_eos(ph, rd, Td);
             T = (float)Td;
         }
+        fl.e[c] = (float)pr_eos(ph, rd, (double)T).e;
         Pr = (float)q.P;
         c2 = (float)q.cs2;
         if (counters) {

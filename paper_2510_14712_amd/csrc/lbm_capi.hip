@@ -18,76 +18,17 @@ using namespace lbm;
 
 // ---------------------------------------------------------------------------
 // Deterministic FP64 reductions: per-block partials (wavefront shuffles, then
-// LDS), then a single block summing the partials in block order.
+// LDS), then a single block summing the partials in a fixed order.
 // ---------------------------------------------------------------------------
 namespace lbm {
-constexpr int RED_BLOCK = 256;
-constexpr int RED_VALS = 7;  // rho, j_x, j_y, j_z, G, non-finite count, inadmissible count
-
-__device__ __forceinline__ double wave_sum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// The admissible set of a cell state: rho > 0 and b rho < 1 (the van der
-// Waals domain, eq. Pvdw), 0 < theta < 1/3 (theta = P/rho; the practical
-// stability bound theta < dx^2/(3 dt^2) of Section 5) and theta + u_a^2 < 1
-// on every axis (the rest factor 1 - theta - u_a^2 of eq. phi stays
-// positive).  Evaluated in FP64 on finite inputs.
+// the counts of non-finite and inadmissible cells for the FP64 inputs of
+// lbm_init (rho, u, T given; P from eq. Pvdw), columns 5 and 6 of the partials,
+// the others zero
 template <int D>
-__device__ __forceinline__ bool admissible(double rho, double theta, const double *u, double b) {
-    bool ok = rho > 0.0 && b * rho < 1.0 && theta > 0.0 && theta < 1.0 / 3.0;
-    for (int a = 0; a < D; a++) ok = ok && theta + u[a] * u[a] < 1.0;
-    return ok;
-}
-
-// per-block partial sums of the RED_VALS values, written by lane k < RED_VALS
-// of the block in a fixed order (wavefront shuffles, then LDS)
-__device__ __forceinline__ void block_partials(double (&acc)[RED_VALS], double *partials) {
-    __shared__ double sh[RED_VALS][RED_BLOCK / 64];
-    int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int k = 0; k < RED_VALS; k++) {
-        double s = wave_sum(acc[k]);
-        if (lane == 0) sh[k][w] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x < RED_VALS) {
-        double s = 0;
-        for (int i = 0; i < RED_BLOCK / 64; i++) s += sh[threadIdx.x][i];
-        partials[(long long)blockIdx.x * RED_VALS + threadIdx.x] = s;
-    }
-}
-
-template <int D, class C>
-__global__ void __launch_bounds__(RED_BLOCK) k_reduce_partials(long long N, Fields<C> fl, double b, double *partials) {
-    double acc[RED_VALS] = {0, 0, 0, 0, 0, 0, 0};
-    for (long long c = blockIdx.x * (long long)RED_BLOCK + threadIdx.x; c < N; c += (long long)gridDim.x * RED_BLOCK) {
-        double rho = fl.rho[c];
-        double G = fl.G[c];
-        double P = fl.P[c];
-        bool bad = !isfinite(rho) || !isfinite(G) || !isfinite(P);
-        acc[0] += rho;
-        double u[3] = {0, 0, 0};
-        for (int a = 0; a < D; a++) {
-            double j = (double)fl.J[a * N + c] + 0.5 * (double)fl.F[a * N + c];
-            acc[1 + a] += j;
-            u[a] = fl.u[a * N + c];
-            bad = bad || !isfinite(j) || !isfinite(u[a]);
-        }
-        acc[4] += G;
-        acc[5] += bad ? 1.0 : 0.0;
-        acc[6] += (!bad && !admissible<D>(rho, P / rho, u, b)) ? 1.0 : 0.0;
-    }
-    block_partials(acc, partials);
-}
-
-// the same counts for the FP64 inputs of lbm_init (rho, u, T given; P from
-// eq. Pvdw), columns 5 and 6 of the partials, the others zero
-template <int D>
-__global__ void __launch_bounds__(RED_BLOCK) k_check_inputs(long long N, Phys<double> ph, const double *rho,
+__global__ void __launch_bounds__(BX) k_check_inputs(long long N, Phys<double> ph, const double *rho,
                                                             const double *u, const double *T, double *partials) {
     double acc[RED_VALS] = {0, 0, 0, 0, 0, 0, 0};
-    for (long long c = blockIdx.x * (long long)RED_BLOCK + threadIdx.x; c < N; c += (long long)gridDim.x * RED_BLOCK) {
+    for (long long c = blockIdx.x * (long long)BX + threadIdx.x; c < N; c += (long long)gridDim.x * BX) {
         const double r = rho[c], t = T[c];
         double uu[3] = {0, 0, 0};
         bool bad = !isfinite(r) || !isfinite(t);
@@ -104,14 +45,14 @@ __global__ void __launch_bounds__(RED_BLOCK) k_check_inputs(long long N, Phys<do
     block_partials(acc, partials);
 }
 
-__global__ void __launch_bounds__(64) k_reduce_final(int nblocks, const double *partials, double *out) {
-    // one wave; lane k < RED_VALS sums column k in block order
-    int k = threadIdx.x;
-    if (k < RED_VALS) {
-        double s = 0;
-        for (int b = 0; b < nblocks; b++) s += partials[(long long)b * RED_VALS + k];
-        out[k] = s;
-    }
+// wavefront k sums column k, lane l the partials l, l + 64, ... (one lane per
+// column reading 1024 partials one after the other took 148 us; now 12 us for 2048)
+__global__ void __launch_bounds__(64 * RED_VALS) k_reduce_final(int nblocks, const double *partials, double *out) {
+    const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double s = 0;
+    for (int b = lane; b < nblocks; b += 64) s += partials[(long long)b * RED_VALS + k];
+    s = wave_sum(s);
+    if (lane == 0) out[k] = s;
 }
 
 // population decode / encode between the storage form and FP64
@@ -143,19 +84,6 @@ __global__ void __launch_bounds__(BX) k_set_pops(Grid g, RefPops ref, const doub
         go[pop_index<Q>(g, i, z, xy)] = S::enc((C)gi[i * g.N + c], (C)ref.g[i]);
     }
 }
-template <int D, class C>
-__global__ void __launch_bounds__(BX) k_export_moments(Grid g, Fields<C> fl, double *rho, double *u, double *T,
-                                                       double *P) {
-    int x = blockIdx.x * BX + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-    if (x >= g.nx) return;
-    long long c = cell_index<D>(g, x, y, z);
-    if (rho) rho[c] = fl.rho[c];
-    if (u)
-        for (int a = 0; a < D; a++) u[a * g.N + c] = fl.u[a * g.N + c];
-    if (T) T[c] = fl.T[c];
-    if (P) P[c] = fl.P[c];
-}
-
 __global__ void k_codec_encode(int kind, const float *x, const float *ref, uint16_t *out, long long n) {
     long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -464,9 +392,9 @@ template <int D, class S> struct Impl {
 
     // counts of non-finite and inadmissible cells of the inputs (blocking)
     static int check_inputs(lbm_ctx *c, const double *rho, const double *u, const double *Tf) {
-        hipLaunchKernelGGL((k_check_inputs<D>), dim3(c->red_blocks), dim3(RED_BLOCK), 0, c->stream,
+        hipLaunchKernelGGL((k_check_inputs<D>), dim3(READ_BLOCKS), dim3(BX), 0, c->stream,
                            (long long)c->grid.N, make_phys<double>(c->p), rho, u, Tf, c->red_partials);
-        hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(64), 0, c->stream, c->red_blocks, c->red_partials,
+        hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(64 * RED_VALS), 0, c->stream, READ_BLOCKS, c->red_partials,
                            c->red_out);
         int rc = last_launch();
         if (rc) return rc;
@@ -485,23 +413,71 @@ template <int D, class S> struct Impl {
         int rc = last_launch();
         return rc ? rc : fused_prepare(c);
     }
-    // count: add the Peng-Robinson Newton iterations to the context's
-    // counters (the step's passes; read-back passes do not count)
-    static int fields_pass(lbm_ctx *c, bool count = false) {
-        Fields<C> fl = get_fields<C>(c);
-        dim3 gr = cell_grid(c);
+    static MomSrc<C> field_moments(lbm_ctx *c) {
+        return MomSrc<C>{get_fields<C>(c).rho, (long long)c->p.nx * c->p.ny, (long long)c->grid.N, D + 1};
+    }
+    // moments and fields of every cell (multi-kernel step)
+    static int fields_pass(lbm_ctx *c) {
+        moments_launch(c);
+        lap_launch(c, field_moments(c));
+        const int rc = fields_launch(c);
+        return rc ? rc : last_launch();
+    }
+    static void moments_launch(lbm_ctx *c) {
         hipLaunchKernelGGL((k_moments<D, S>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, c->ref,
-                           (const T *)c->f[c->cur], fl, c->pulled);
-        hipLaunchKernelGGL((k_lap<D, C>), gr, dim3(BX), 0, c->stream, c->grid, fl);
+                           (const T *)c->f[c->cur], get_fields<C>(c), c->pulled);
+    }
+    static void lap_launch(lbm_ctx *c, const MomSrc<C> &m) {
+        hipLaunchKernelGGL((k_lap<D, C>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, m, get_fields<C>(c).lap);
+    }
+    static bool warm_start(const lbm_ctx *c) { return c->p.eos == LBM_EOS_PR_PREV && c->T_valid; }
+    static int fields_launch(lbm_ctx *c) {
+        int rc = LBM_OK;
+        if (lbm_eos_uses_mlp(c->p.eos)) rc = launch_fields_mlp<D, C>(c, get_fields<C>(c));
+        else
+            hipLaunchKernelGGL((k_fields<D, C>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, make_phys<C>(c->p),
+                               field_moments(c), get_fields<C>(c), warm_start(c) ? 1 : 0, c->mlp_counters);
+        c->T_valid = true;
+        return rc;
+    }
+    // The moments of the current state for a read-back.  The fused step's side
+    // channel holds them (20 bytes per cell against the 2 Q populations that
+    // k_moments reads, 5.1 ms at 512^3 cells in BF16); where the next step would
+    // complete them on load, k_complete does so into the field arrays (1.5 ms).
+    static MomSrc<C> state_moments(lbm_ctx *c) {
+        if (!c->fused) {
+            moments_launch(c);
+            return field_moments(c);
+        }
+        const long long plane = (long long)c->p.nx * c->p.ny;
+        const bool pending = c->mc_pending;  // surrogate form: its pass completes them
+        const int at = pending ? 1 - c->mcc : c->mcc;
+        if (!pending && !kfold(c)) return MomSrc<C>{(const C *)c->Mc[at], 5 * plane, plane, 4};
+        using TL = TileOf<S, false>;
+        static_assert(std::is_same<TL, TileOf<S, true>>::value, "one tile for both forms");
+        hipLaunchKernelGGL((k_complete<D, TL, C>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, c->ntx, c->nty,
+                           c->nseg, (const C *)c->Mc[at], (const C *)c->IN[at], get_fields<C>(c));
+        return field_moments(c);
+    }
+    // rho, u, T, P to the caller's arrays (any null) or the conservation sums
+    // to the partials
+    static int read_back(lbm_ctx *c, const ReadOut &o) {
+        const MomSrc<C> m = state_moments(c);
+        lap_launch(c, m);
+        Fields<C> fl = get_fields<C>(c);
         if (lbm_eos_uses_mlp(c->p.eos)) {
-            int rc = launch_fields_mlp<D, C>(c, fl, count);
+            const int rc = launch_readback_mlp<D, C>(c, m, fl, o);
             if (rc) return rc;
         } else {
-            hipLaunchKernelGGL((k_fields<D, C>), gr, dim3(BX), 0, c->stream, c->grid, make_phys<C>(c->p), fl,
-                               (c->p.eos == LBM_EOS_PR_PREV && c->T_valid) ? 1 : 0,
-                               count ? c->mlp_counters : (unsigned long long *)nullptr);
+            const int warm = warm_start(c) ? 1 : 0;
+            if (o.partials)
+                hipLaunchKernelGGL((k_readback<D, C, true>), dim3(READ_BLOCKS), dim3(BX), 0, c->stream, c->grid,
+                                   make_phys<C>(c->p), m, fl.lap, fl.T, warm, o);
+            else
+                hipLaunchKernelGGL((k_readback<D, C, false>), dim3(READ_BLOCKS), dim3(BX), 0, c->stream, c->grid,
+                                   make_phys<C>(c->p), m, fl.lap, fl.T, warm, o);
+            c->T_valid = c->T_valid || lbm_eos_is_pr(c->p.eos);
         }
-        c->T_valid = true;
         return last_launch();
     }
     // shock-capturing passes over the fields of the step; returns the filtered
@@ -510,7 +486,7 @@ template <int D, class S> struct Impl {
         *fS = *fs = nullptr;
         if (!c->sc) return;
         Fields<C> fl = get_fields<C>(c);
-        dim3 gr = cell_grid(c);
+        const dim3 gr = cell_grid(c);
         hipLaunchKernelGGL((k_sc_grad<D, C>), gr, dim3(BX), 0, c->stream, c->grid, make_phys<C>(c->p), fl);
         hipLaunchKernelGGL((k_sc_d4<D, C>), gr, dim3(BX), 0, c->stream, c->grid, fl.sc[0], fl.sc[1], fl.sc[2],
                            fl.sc[3]);
@@ -553,14 +529,13 @@ template <int D, class S> struct Impl {
     }
     static int step(lbm_ctx *c, int n) {
         Fields<C> fl = get_fields<C>(c);
-        dim3 gr = cell_grid(c);
         for (int s = 0; s < n; s++) {
             int rc;
             if (c->fused) {
                 fused_launch(c);
                 rc = last_launch();
             } else {
-                rc = fields_pass(c, true);
+                rc = fields_pass(c);
                 if (rc) return rc;
                 const C *fS, *fs;
                 sc_passes(c, &fS, &fs);
@@ -614,20 +589,14 @@ template <int D, class S> struct Impl {
         }
         double acc[4] = {0, 0, 0, 0};
         Fields<C> fl = get_fields<C>(c);
-        dim3 gr = cell_grid(c);
         int rc = LBM_OK;
         for (int s = 0; s < n && rc == LBM_OK; s++) {
             (void)hipEventRecord(ev[0], c->stream);
-            hipLaunchKernelGGL((k_moments<D, S>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, c->ref,
-                               (const T *)c->f[c->cur], fl, c->pulled);
+            moments_launch(c);
             (void)hipEventRecord(ev[1], c->stream);
-            hipLaunchKernelGGL((k_lap<D, C>), gr, dim3(BX), 0, c->stream, c->grid, fl);
+            lap_launch(c, field_moments(c));
             (void)hipEventRecord(ev[2], c->stream);
-            if (lbm_eos_uses_mlp(c->p.eos)) rc = launch_fields_mlp<D, C>(c, fl, true);
-            else
-                hipLaunchKernelGGL((k_fields<D, C>), gr, dim3(BX), 0, c->stream, c->grid, make_phys<C>(c->p), fl,
-                                   (c->p.eos == LBM_EOS_PR_PREV && c->T_valid) ? 1 : 0, c->mlp_counters);
-            c->T_valid = true;
+            rc = fields_launch(c);
             const C *fS, *fs;
             sc_passes(c, &fS, &fs);  // timed with the fields kind
             (void)hipEventRecord(ev[3], c->stream);
@@ -648,11 +617,7 @@ template <int D, class S> struct Impl {
         return rc;
     }
     static int moments(lbm_ctx *c, double *rho, double *u, double *Tf, double *P) {
-        int rc = fields_pass(c);
-        if (rc) return rc;
-        hipLaunchKernelGGL((k_export_moments<D, C>), cell_grid(c), dim3(BX), 0, c->stream, c->grid, get_fields<C>(c),
-                           rho, u, Tf, P);
-        return last_launch();
+        return read_back(c, ReadOut{rho, u, Tf, P, nullptr});
     }
     static int get_pops(lbm_ctx *c, double *f, double *g) {
         hipLaunchKernelGGL((k_get_pops<D, S>), cell_grid(c), dim3(BX), 0, c->stream, c->grid, c->ref,
@@ -733,11 +698,9 @@ template <int D, class S> struct Impl {
         c->in_bytes = sizeof(C) * (size_t)ntiles * c->nlay * 5 * TL::NR;
     }
     static int conservation(lbm_ctx *c, double *host_out) {
-        int rc = fields_pass(c);
+        int rc = read_back(c, ReadOut{nullptr, nullptr, nullptr, nullptr, c->red_partials});
         if (rc) return rc;
-        hipLaunchKernelGGL((k_reduce_partials<D, C>), dim3(c->red_blocks), dim3(RED_BLOCK), 0, c->stream,
-                           (long long)c->grid.N, get_fields<C>(c), c->p.b, c->red_partials);
-        hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(64), 0, c->stream, c->red_blocks, c->red_partials,
+        hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(64 * RED_VALS), 0, c->stream, READ_BLOCKS, c->red_partials,
                            c->red_out);
         rc = last_launch();
         if (rc) return rc;
@@ -860,12 +823,7 @@ int lbm_create(const lbm_params *params, lbm_ctx **out) {
     int cb = params->storage == LBM_STORE_F64 ? 8 : 4;
     make_ref(*params, c->D, c->ref);
     size_t pop_bytes = (size_t)c->Q * N * sb;
-    // field arrays: rho, J[D], G, lap, u[D], F[D], Lam[D], T, P, h, cs2, with
-    // Peng-Robinson e(rho, T), and the four shock-capturing work arrays when
-    // that scheme is on
     c->sc = params->sc_cmu > 0 || params->sc_ceta > 0 || params->sc_ck > 0;
-    size_t nfield = (size_t)(8 + 4 * c->D + (lbm_eos_is_pr(params->eos) ? 1 : 0) + (c->sc ? 4 : 0));
-    size_t field_bytes = nfield * N * cb;
     // the single-pass step covers periodic z (and every D = 2 lattice)
     // with the van der Waals equation of state, without shock capturing
     c->fused = (c->D == 2 || params->bc[2] == LBM_BC_PERIODIC) && !c->sc && !lbm_eos_is_pr(params->eos) &&
@@ -881,6 +839,13 @@ int lbm_create(const lbm_params *params, lbm_ctx **out) {
             c->fused = false;
     }
     if (!c->fused) c->folded = false;
+    // field arrays: rho, J[D], G, lap (all that a read-back of the fused path
+    // uses); the multi-kernel path's also u[D], F[D], Lam[D], T, P, h, cs2, with
+    // Peng-Robinson e(rho, T), and the four shock-capturing work arrays when
+    // that scheme is on
+    size_t nfield = (size_t)(3 + c->D);
+    if (!c->fused) nfield += (size_t)(4 + 3 * c->D + (lbm_eos_is_pr(params->eos) ? 1 : 0) + (c->sc ? 4 : 0));
+    const size_t field_bytes = nfield * N * cb;
     // The large buffers come from one allocation, carved at 2 MiB boundaries:
     // the population sets (one buffer per ping-pong slot holds both sets, f_i
     // and g_i side by side; the g pointer is the f buffer offset by one
@@ -904,9 +869,8 @@ int lbm_create(const lbm_params *params, lbm_ctx **out) {
     constexpr size_t ALIGN = (size_t)1 << 21;
     size_t total = 0;
     for (const Part &pt : parts) total += (pt.bytes + ALIGN - 1) / ALIGN * ALIGN;
-    c->red_blocks = 1024;
     bool ok = hipMalloc(&c->block, total) == hipSuccess &&
-              hipMalloc((void **)&c->red_partials, sizeof(double) * RED_VALS * c->red_blocks) == hipSuccess &&
+              hipMalloc((void **)&c->red_partials, sizeof(double) * RED_VALS * READ_BLOCKS) == hipSuccess &&
               hipMalloc((void **)&c->red_out, sizeof(double) * RED_VALS) == hipSuccess &&
               hipMalloc((void **)&c->mlp_counters, LBM_COUNTER_BYTES) == hipSuccess &&
               hipMalloc((void **)&c->mlp_params, sizeof(float) * (LBM_MLP_NPARAMS + 64)) == hipSuccess &&

@@ -418,8 +418,7 @@ __global__ void __launch_bounds__(256, 2) k_eos_surrogate(Grid g, Phys<float> ph
         const int m = r / mlp::H, k = r % mlp::H;
         sW2[m * W2LD + k] = W2b[m * mlp::H + mlp::w2_perm_col(k)];
     }
-    const mlp::Net net{sNet + mlp::OFF_W1, sNet + mlp::OFF_B1, sW2, nullptr, sNet + mlp::OFF_W2,
-                       sNet + mlp::OFF_W2 + mlp::H, sNet + mlp::OFF_W2 + 2 * mlp::H, W2LD};
+    const mlp::Net net{sW2, sNet + mlp::OFF_W2, sNet + mlp::OFF_W2 + mlp::H, sNet + mlp::OFF_W2 + 2 * mlp::H, W2LD};
 
     const int nx = g.nx, ny = g.ny, nz = D == 3 ? g.nz : 1;
     const unsigned plane = (unsigned)nx * (unsigned)ny;
@@ -1545,6 +1544,41 @@ __global__ void __launch_bounds__(BX) k_fused_fixup(Grid g, int ntx, int nty, in
 #pragma unroll
         for (int k = 0; k < 5; k++) mc(z, k) = v[k];
     }
+}
+
+// Complete moments rho, J, G of every cell into the field arrays, for a
+// read-back of a state whose side channel holds partial sums: a perimeter cell
+// adds its inbound slots with the fix-up's terms, order and rounding; the
+// segment-end planes (D = 3) are complete already.
+template <int D, class TL, class C>
+__global__ void __launch_bounds__(BX) k_complete(Grid g, int ntx, int nty, int nseg, const C *__restrict__ Mc,
+                                                 const C *__restrict__ IN, Fields<C> fl) {
+    int x, y, z;
+    if (!flat_cell(g, x, y, z)) return;
+    const int tx = x / TL::TX, ty = y / TL::TY, lx = x - tx * TL::TX, ly = y - ty * TL::TY;
+    const int w = min(TL::TX, g.nx - tx * TL::TX), h = min(TL::TY, g.ny - ty * TL::TY);
+    bool add = lx == 0 || lx == w - 1 || ly == 0 || ly == h - 1;
+    if (D == 3) {
+        const int s = seg_of(z, g.nz, nseg);
+        add = add && z != seg_lo(s, g.nz, nseg) && z != seg_lo(s + 1, g.nz, nseg) - 1;
+    }
+    const size_t plane = (size_t)g.nx * g.ny, xy = x + (size_t)g.nx * y;
+    const C *mc = Mc + (size_t)z * 5 * plane + xy;
+    const C *in = IN + ((size_t)z * ((unsigned)ntx * (unsigned)nty) + (unsigned)(ty * ntx + tx)) * 5u * TL::NR;
+    C v[5];
+#pragma unroll
+    for (int k = 0; k < 5; k++) v[k] = mc[k * plane];
+    if (add) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) {
+            if (w >= 2 && h >= 2) v[k] += inbound_sum_2x2<TL>(in + k * TL::NR, lx, ly, w, h);
+            else v[k] += inbound_sum<TL>(in + k * TL::NR, lx, ly, w, h);
+        }
+    }
+    const long long c = cell_index<D>(g, x, y, z);
+    fl.rho[c] = v[0];
+    for (int a = 0; a < D; a++) fl.J[a * g.N + c] = v[1 + a];
+    fl.G[c] = v[4];
 }
 
 // Complete moments of a stored state (after init or set_populations) in the

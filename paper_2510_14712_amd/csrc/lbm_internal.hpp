@@ -26,7 +26,6 @@ struct lbm_ctx {
     long long steps_done = 0;         // steps since the last init / set_populations (check interval)
     bool T_valid = false;             // the field array T holds the current state's temperature
     bool mlp_ready = false;
-    int red_blocks = 0;
     double *red_partials = nullptr;
     double *red_out = nullptr;
     unsigned long long *mlp_counters = nullptr;  // [slot][8]: fallbacks, evaluations, Newton iterations, cells
@@ -84,6 +83,8 @@ template <class C> static inline lbm::Fields<C> get_fields(lbm_ctx *c) {
 // Record a failed HIP call's message for lbm_last_error(); returns the status.
 int lbm_note(hipError_t e);
 
-// surrogate-EOS variant of the per-cell fields pass (defined with the MLP
-// code); count: add Newton iterations to the context's counters
-template <int D, class C> int launch_fields_mlp(lbm_ctx *c, lbm::Fields<C> fl, bool count);
+// surrogate-EOS variants of the fields pass and of the read-back (defined with
+// the MLP code)
+template <int D, class C> int launch_fields_mlp(lbm_ctx *c, lbm::Fields<C> fl);
+template <int D, class C>
+int launch_readback_mlp(lbm_ctx *c, const lbm::MomSrc<C> &m, lbm::Fields<C> fl, const lbm::ReadOut &o);

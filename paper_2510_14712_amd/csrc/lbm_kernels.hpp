@@ -29,6 +29,15 @@ template <class C> struct Fields {
     C *sc[4];            // shock-capturing work arrays (null when off)
 };
 
+// where a pass finds the moments rho, J, G of the state: the field arrays, or
+// the fused step's side channel.  Value k of cell xy of plane z lies at
+// p[z zs + k ks + xy]; k = 0: rho, 1 .. D: J, kG: G.
+template <class C> struct MomSrc {
+    const C *p;
+    long long zs, ks;
+    int kG;
+};
+
 template <int D> __device__ __forceinline__ long long cell_index(const Grid &g, int x, int y, int z) {
     return (long long)x + (long long)g.nx * ((long long)y + (long long)g.ny * z);
 }
@@ -147,14 +156,47 @@ __global__ void __launch_bounds__(BX) k_moments(Grid g, RefPops ref, const typen
 }
 
 template <int D, class C>
-__global__ void __launch_bounds__(BX) k_lap(Grid g, Fields<C> fl) {
-    int x = blockIdx.x * BX + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-    if (x >= g.nx) return;
-    long long c = cell_index<D>(g, x, y, z);
-    C r0 = fl.rho[c], s = 0;
-    for (int a = 0; a < D; a++)
-        s += fl.rho[nb_axis<D>(g, x, y, z, a, 1)] + fl.rho[nb_axis<D>(g, x, y, z, a, -1)] - C(2) * r0;
-    fl.lap[c] = s;
+__global__ void __launch_bounds__(BX) k_lap(Grid g, MomSrc<C> m, C *__restrict__ lap) {
+    int x, y, z;
+    if (!flat_cell(g, x, y, z)) return;
+    auto rho = [&](int xx, int yy, int zz) { return m.p[zz * m.zs + (xx + (long long)g.nx * yy)]; };
+    const C r0 = rho(x, y, z);
+    C s = 0;
+    for (int a = 0; a < D; a++) {
+        int p[3] = {x, y, z}, q[3] = {x, y, z};
+        const int n = a == 0 ? g.nx : (a == 1 ? g.ny : g.nz), cl = a == 0 ? g.clampx : (a == 1 ? g.clampy : g.clampz);
+        p[a] = wrap1(p[a] + 1, n, cl);
+        q[a] = wrap1(q[a] - 1, n, cl);
+        s += rho(p[0], p[1], p[2]) + rho(q[0], q[1], q[2]) - C(2) * r0;
+    }
+    lap[cell_index<D>(g, x, y, z)] = s;
+}
+
+// density, force, velocity and internal energy of a cell from its moments and
+// the Laplacian (eqs. FK, def_u, def_E)
+template <class C> struct CellKin {
+    C rho, inv_rho, J[3], G, u[3], F[3], e;
+};
+template <int D, class C>
+__device__ __forceinline__ CellKin<C> cell_kin(const Grid &g, const Phys<C> &ph, const MomSrc<C> &m,
+                                               const C *__restrict__ lap, int x, int y, int z) {
+    const long long mc = z * m.zs + (x + (long long)g.nx * y);
+    CellKin<C> k;
+    k.rho = m.p[mc];
+    k.inv_rho = C(1) / k.rho;
+    C uF = 0, u2 = 0;
+    for (int a = 0; a < D; a++) {
+        C dl = C(0.5) * (lap[nb_axis<D>(g, x, y, z, a, 1)] - lap[nb_axis<D>(g, x, y, z, a, -1)]);
+        k.J[a] = m.p[mc + (a + 1) * m.ks];
+        k.F[a] = ph.kappa * k.rho * dl;                     // eq. FK
+        k.u[a] = (k.J[a] + C(0.5) * k.F[a]) * k.inv_rho;    // eq. def_u
+        uF += k.u[a] * k.F[a];
+        u2 += k.u[a] * k.u[a];
+    }
+    k.G = m.p[mc + m.kG * m.ks];
+    C E = (k.G + C(0.5) * uF) * k.inv_rho;                  // eq. def_E
+    k.e = E - C(0.5) * u2;
+    return k;
 }
 
 // sum over a wavefront of a per-lane count, added once per wavefront
@@ -169,29 +211,22 @@ __device__ __forceinline__ void wave_count(unsigned long long *dst, unsigned v) 
 // or from the cell's temperature of the previous step (warm = 1);
 // counters [2] counts the iterations, [3] the cells (may be null)
 template <int D, class C>
-__global__ void __launch_bounds__(BX) k_fields(Grid g, Phys<C> ph, Fields<C> fl, int warm,
+__global__ void __launch_bounds__(BX) k_fields(Grid g, Phys<C> ph, MomSrc<C> m, Fields<C> fl, int warm,
                                                unsigned long long *counters) {
-    int x = blockIdx.x * BX + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-    const bool active = x < g.nx;
+    int x, y, z;
+    const bool active = flat_cell(g, x, y, z);
     if (ph.pr && counters) {
         // the wavefront's lanes all take part in the count below
-        if (!active) x = g.nx - 1;
+        if (!active) {
+            x = g.nx - 1;
+            y = g.ny - 1;
+        }
     } else if (!active) {
         return;
     }
     long long c = cell_index<D>(g, x, y, z);
-    C rho = fl.rho[c];
-    C inv_rho = C(1) / rho;
-    C u[3], F[3], uF = 0, u2 = 0;
-    for (int a = 0; a < D; a++) {
-        C dl = C(0.5) * (fl.lap[nb_axis<D>(g, x, y, z, a, 1)] - fl.lap[nb_axis<D>(g, x, y, z, a, -1)]);
-        F[a] = ph.kappa * rho * dl;                          // eq. FK
-        u[a] = (fl.J[a * g.N + c] + C(0.5) * F[a]) * inv_rho;  // eq. def_u
-        uF += u[a] * F[a];
-        u2 += u[a] * u[a];
-    }
-    C E = (fl.G[c] + C(0.5) * uF) * inv_rho;                  // eq. def_E
-    C e = E - C(0.5) * u2;
+    const CellKin<C> k = cell_kin<D>(g, ph, m, fl.lap, x, y, z);
+    const C rho = k.rho, inv_rho = k.inv_rho, e = k.e;
     C T, P, cs2;
     if (ph.pr) {
         int it = 0;
@@ -214,15 +249,126 @@ __global__ void __launch_bounds__(BX) k_fields(Grid g, Phys<C> ph, Fields<C> fl,
     }
     C theta = P * inv_rho;
     for (int a = 0; a < D; a++) {
-        fl.u[a * g.N + c] = u[a];
-        fl.F[a * g.N + c] = F[a];
+        fl.u[a * g.N + c] = k.u[a];
+        fl.F[a * g.N + c] = k.F[a];
         // Lambda_a = rho u_a^3 + 3 rho u_a (theta - 1/3)   (eq. correction)
-        fl.Lam[a * g.N + c] = rho * u[a] * (u[a] * u[a] + C(3) * (theta - C(1.0 / 3.0)));
+        fl.Lam[a * g.N + c] = rho * k.u[a] * (k.u[a] * k.u[a] + C(3) * (theta - C(1.0 / 3.0)));
     }
     fl.T[c] = T;
     fl.P[c] = P;
     fl.h[c] = e + theta;                                       // eq. enthalpy
     fl.cs2[c] = cs2;
+}
+
+// ---------------------------------------------------------------------------
+// Read-back of a state: one pass from the moments and the Laplacian straight
+// to the caller's FP64 arrays (any null) and, with SUMS, to the conservation
+// partials; no field array is written but, with Peng-Robinson, T (the next
+// warm start).  Bound by HBM: 24 bytes read (FP32) and 48 written per cell
+// (256^3 cells: 0.28 ms, the sums 0.14 ms; through the field arrays the fields
+// pass took 0.23 ms and each of the two that read them 0.20 to 0.23).  A block takes a contiguous run of 256-cell units, neighbouring runs on one XCD,
+// whose L2 then holds the Laplacian rows that they share.
+constexpr int RED_VALS = 7;  // rho, j_x, j_y, j_z, G, non-finite count, inadmissible count
+constexpr int READ_BLOCKS = 2048;  // 8 blocks of 256 threads per compute unit
+
+__device__ __forceinline__ double wave_sum(double v) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// The admissible set of a cell state: rho > 0 and b rho < 1 (the van der
+// Waals domain, eq. Pvdw), 0 < theta < 1/3 (theta = P/rho; the practical
+// stability bound theta < dx^2/(3 dt^2) of Section 5) and theta + u_a^2 < 1
+// on every axis (the rest factor 1 - theta - u_a^2 of eq. phi stays
+// positive).  Evaluated in FP64 on finite inputs.
+template <int D>
+__device__ __forceinline__ bool admissible(double rho, double theta, const double *u, double b) {
+    bool ok = rho > 0.0 && b * rho < 1.0 && theta > 0.0 && theta < 1.0 / 3.0;
+    for (int a = 0; a < D; a++) ok = ok && theta + u[a] * u[a] < 1.0;
+    return ok;
+}
+
+// per-block partial sums of the RED_VALS values, written by lane k < RED_VALS
+// of the block in a fixed order (wavefront shuffles, then LDS)
+__device__ __forceinline__ void block_partials(double (&acc)[RED_VALS], double *partials) {
+    __shared__ double sh[RED_VALS][BX / 64];
+    int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int k = 0; k < RED_VALS; k++) {
+        double s = wave_sum(acc[k]);
+        if (lane == 0) sh[k][w] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < RED_VALS) {
+        double s = 0;
+        for (int i = 0; i < BX / 64; i++) s += sh[threadIdx.x][i];
+        partials[(long long)blockIdx.x * RED_VALS + threadIdx.x] = s;
+    }
+}
+
+struct ReadOut {
+    double *rho, *u, *T, *P;  // the caller's arrays, or null
+    double *partials;         // [READ_BLOCKS][RED_VALS]
+};
+// units [u0, u1) of this block
+__device__ __forceinline__ void read_units(const Grid &g, long long &u0, long long &u1, unsigned &per_plane) {
+    per_plane = ((unsigned)g.nx * (unsigned)g.ny + BX - 1) / BX;
+    const long long units = (long long)per_plane * g.nz;
+    const unsigned b = (blockIdx.x & 7) * (READ_BLOCKS / 8) + (blockIdx.x >> 3);
+    u0 = units * b / READ_BLOCKS;
+    u1 = units * (b + 1) / READ_BLOCKS;
+}
+template <int D, class C, bool SUMS>
+__device__ __forceinline__ void read_cell(const Grid &g, const CellKin<C> &k, C T, C P, long long c, double b,
+                                          const ReadOut &o, double (&acc)[RED_VALS]) {
+    if (o.rho) o.rho[c] = k.rho;
+    if (o.u)
+        for (int a = 0; a < D; a++) o.u[a * g.N + c] = k.u[a];
+    if (o.T) o.T[c] = T;
+    if (o.P) o.P[c] = P;
+    if constexpr (SUMS) {
+        const double rho = k.rho, G = k.G, Pd = P;
+        bool bad = !isfinite(rho) || !isfinite(G) || !isfinite(Pd);
+        double u[3] = {0, 0, 0};
+        acc[0] += rho;
+        for (int a = 0; a < D; a++) {
+            const double j = (double)k.J[a] + 0.5 * (double)k.F[a];
+            acc[1 + a] += j;
+            u[a] = k.u[a];
+            bad = bad || !isfinite(j) || !isfinite(u[a]);
+        }
+        acc[4] += G;
+        acc[5] += bad ? 1.0 : 0.0;
+        acc[6] += (!bad && !admissible<D>(rho, Pd / rho, u, b)) ? 1.0 : 0.0;
+    }
+}
+template <int D, class C, bool SUMS>
+__global__ void __launch_bounds__(BX) k_readback(Grid g, Phys<C> ph, MomSrc<C> m, const C *__restrict__ lap,
+                                                 C *__restrict__ Tf, int warm, ReadOut o) {
+    double acc[RED_VALS] = {0, 0, 0, 0, 0, 0, 0};
+    long long u0, u1;
+    unsigned per_plane;
+    read_units(g, u0, u1, per_plane);
+    for (long long un = u0; un < u1; un++) {
+        const int z = (int)((unsigned long long)un / per_plane);
+        const unsigned p = (unsigned)(un - (long long)z * per_plane) * BX + threadIdx.x;
+        const int y = (int)(p / (unsigned)g.nx), x = (int)(p - (unsigned)y * (unsigned)g.nx);
+        if (y >= g.ny) continue;
+        const long long c = cell_index<D>(g, x, y, z);
+        const CellKin<C> k = cell_kin<D>(g, ph, m, lap, x, y, z);
+        C T, P;
+        if (ph.pr) {
+            int it = 0;
+            const double Td = pr_temperature(ph, (double)k.rho, (double)k.e, warm ? (double)Tf[c] : 0.0, it);
+            T = (C)Td;
+            P = (C)pr_eos(ph, (double)k.rho, Td).P;
+            Tf[c] = T;
+        } else {
+            T = (k.e + ph.a * k.rho) * ph.inv_cv;   // eq. lbm_temp
+            P = vdw_pressure(ph, k.rho, T);         // eq. Pvdw
+        }
+        read_cell<D, C, SUMS>(g, k, T, P, c, (double)ph.b, o, acc);
+    }
+    if constexpr (SUMS) block_partials(acc, o.partials);
 }
 
 // ---------------------------------------------------------------------------

@@ -1,11 +1,11 @@
 // Learned equation-of-state surrogate (rho, e) -> (T, P, c_s^2): a
 // 2 -> 64 -> 64 -> 3 ReLU network standing in for the caloric inversion of
 // Section 3.2 (explicit for van der Waals, eq. lbm_temp; iterative for a
-// general equation of state).  Inference runs inside the per-cell fields pass
+// general equation of state).  Inference runs inside the per-cell passes
 // with a residual check and an exact FP64 Newton fallback; training uses the
 // library's own forward, backward and Adam kernels.
 //
-// One wavefront handles 64 samples (cells).  The 64x64 hidden layer and the
+// In training one wavefront handles 64 samples.  The 64x64 hidden layer and the
 // two 64x64x64 products of the backward pass run through wave_gemm64: BF16
 // MFMA (v_mfma_f32_32x32x16_bf16, FP32 accumulate) or FP32 on the vector ALU,
 // both returning the result in the MFMA accumulator layout:
@@ -13,6 +13,7 @@
 //   row 32 mt + 8 (v / 4) + 4 (l / 32) + v % 4, column 32 nt + l % 32.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include <cmath>
@@ -72,164 +73,164 @@ __device__ __forceinline__ void wave_gemm64(const float *A, int ai, int ak, cons
     }
 }
 
-// Forward pass of one wavefront through LDS (the FP32 reference form of the
-// network on the vector ALU, MFMA = false).  x0, x1: normalised inputs of this
-// lane's sample; P: FP32 parameter vector; lds: 64 x LD floats private to the
-// wave.  Returns the normalised outputs.  Every lane of the wave must call.
-template <bool MFMA>
-__device__ __forceinline__ void forward_wave_lds(float x0, float x1, const float *__restrict__ P, float *lds,
-                                                 float y[3]) {
-    const int lane = threadIdx.x & 63;
-    for (int j = 0; j < H; j++) {
-        float z = fmaf(P[OFF_W1 + 2 * j], x0, fmaf(P[OFF_W1 + 2 * j + 1], x1, P[OFF_B1 + j]));
-        lds[lane * LD + j] = relu(z);
-    }
-    __syncthreads();
-    float acc[64];
-    // Z2(b, n) = sum_k H1(b, k) W2(n, k)
-    wave_gemm64<MFMA>(lds, LD, 1, P + OFF_W2, 1, H, acc);
-    __syncthreads();
-    for (int t = 0; t < 4; t++)
-        for (int v = 0; v < 16; v++) {
-            const int r = acc_row(t >> 1, v, lane), cidx = acc_col(t & 1, lane);
-            lds[r * LD + cidx] = relu(acc[t * 16 + v] + P[OFF_B2 + cidx]);
-        }
-    __syncthreads();
-    for (int k = 0; k < 3; k++) {
-        float s = P[OFF_B3 + k];
-        for (int n = 0; n < H; n++) s = fmaf(P[OFF_W3 + k * H + n], lds[lane * LD + n], s);
-        y[k] = s;
-    }
-    __syncthreads();
-}
-
 // ---------------------------------------------------------------------------
-// stand-alone forward: grid ceil(B / 64) blocks of one wave
-template <bool MFMA>
-__global__ void __launch_bounds__(64) k_forward(const float *P, const float *norm, const float *x, float *y, int B) {
-    __shared__ float lds[64 * LD];
-    const int b = blockIdx.x * 64 + threadIdx.x;
-    const int bc = b < B ? b : B - 1;
-    float x0, x1, o[3];
-    normalise(norm, x[2 * bc], x[2 * bc + 1], x0, x1);
-    if constexpr (MFMA) forward_wave<3>(x0, x1, net_of(P, nullptr), o);
-    else forward_wave_lds<false>(x0, x1, P, lds, o);
-    if (b < B)
-        for (int k = 0; k < 3; k++) y[3 * b + k] = o[k] * norm[5 + 2 * k] + norm[4 + 2 * k];
+// Stand-alone forward.  A workgroup of four wavefronts puts the network into
+// LDS and takes blocks of 4 x 32 NT samples in turn; NT = 4 once every compute
+// unit has a workgroup with it, else 2 (more wavefronts, less work each).
+constexpr int FWD_BLOCKS = 1024;  // four workgroups per compute unit
+template <bool F32, int NT>
+__global__ void __launch_bounds__(256, 2) k_forward(const float *__restrict__ P, const float *__restrict__ norm,
+                                                 const float *__restrict__ x, float *__restrict__ y, int B) {
+    __shared__ __attribute__((aligned(16))) NetLds<3, F32> net;
+    net_to_lds(net, P, threadIdx.x, 256);
+    __syncthreads();
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (long long b0 = (blockIdx.x * 4ll + w) * (32 * NT); b0 < B; b0 += gridDim.x * 4ll * (32 * NT)) {
+        float x0[NT / 2], x1[NT / 2], o[NT / 2][3];
+#pragma unroll
+        for (int p = 0; p < NT / 2; p++) {
+            const long long b = min(b0 + 64 * p + lane, (long long)B - 1);
+            normalise(norm, x[2 * b], x[2 * b + 1], x0[p], x1[p]);
+        }
+        forward_tiles<3, F32, NT>(x0, x1, net, o);
+#pragma unroll
+        for (int p = 0; p < NT / 2; p++) {
+            const long long b = b0 + 64 * p + lane;
+            if (b < B)
+                for (int k = 0; k < 3; k++) y[3 * b + k] = o[p][k] * norm[5 + 2 * k] + norm[4 + 2 * k];
+        }
+    }
 }
 
-// stand-alone forward in the surrogate pass's form (both hidden layers on
-// BF16 MFMA, W2 columns permuted): grid ceil(B / 64) blocks of one wave
-__global__ void __launch_bounds__(64) k_forward_l1mfma(const float *P, const float *norm, const float *x, float *y,
-                                                       int B) {
+// the surrogate pass's form (both hidden layers on BF16 MFMA, W2 columns
+// permuted), four wavefronts per workgroup, 64 samples each in turn
+__global__ void __launch_bounds__(256, 2) k_forward_l1mfma(const float *__restrict__ P, const float *__restrict__ norm,
+                                                        const float *__restrict__ x, float *__restrict__ y, int B) {
     __shared__ __attribute__((aligned(16))) uint16_t sW2[H * 72];
-    for (int r = threadIdx.x; r < H * H; r += 64)
+    __shared__ float sOut[4 * H + 4];  // b2, w3, b3
+    for (int r = threadIdx.x; r < H * H; r += 256)
         sW2[(r / H) * 72 + r % H] = bf16_hw(P[OFF_W2 + (r / H) * H + w2_perm_col(r % H)]);
+    for (int r = threadIdx.x; r < 4 * H + 3; r += 256) sOut[r] = P[OFF_B2 + r];
     __syncthreads();
-    const Net net{P + OFF_W1, P + OFF_B1, sW2, nullptr, P + OFF_B2, P + OFF_W3, P + OFF_B3, 72};
+    const Net net{sW2, sOut, sOut + H, sOut + 4 * H, 72};
     const L1Ops l1 = l1_operands(P + OFF_W1, P + OFF_B1);
-    const int b = blockIdx.x * 64 + threadIdx.x;
-    const int bc = b < B ? b : B - 1;
-    float x0, x1, o[3];
-    normalise(norm, x[2 * bc], x[2 * bc + 1], x0, x1);
-    forward_wave_l1mfma<3>(x0, x1, net, l1, o);
-    if (b < B)
-        for (int k = 0; k < 3; k++) y[3 * b + k] = o[k] * norm[5 + 2 * k] + norm[4 + 2 * k];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (long long b0 = (blockIdx.x * 4ll + w) * 64; b0 < B; b0 += gridDim.x * 256ll) {
+        const long long b = b0 + lane, bc = b < B ? b : B - 1;
+        float x0, x1, o[3];
+        normalise(norm, x[2 * bc], x[2 * bc + 1], x0, x1);
+        forward_wave_l1mfma<3>(x0, x1, net, l1, o);
+        if (b < B)
+            for (int k = 0; k < 3; k++) y[3 * b + k] = o[k] * norm[5 + 2 * k] + norm[4 + 2 * k];
+    }
 }
 
 // ---------------------------------------------------------------------------
-// Per-cell fields with the surrogate: as the exact fields pass, but T, P and
-// c_s^2 come from the network; a cell whose caloric residual
-// |e(rho, T_hat) - e| / (c_v T_hat) exceeds tol (or is not finite) takes one
-// FP64 Newton step on e(rho, T) = e from T_hat -- exact for van der Waals,
-// whose e is linear in T -- and the closed forms for P and c_s^2.
-constexpr int MLP_BLOCK = 128;  // two waves: 2 x 16.6 KB of LDS per workgroup
-
-// With the Peng-Robinson equation of state the residual is taken with
-// e(rho, T_hat) and c_v(rho, T_hat) in FP64, and a failing cell runs Newton's
-// method from T_hat to convergence (counters[2], [3]: iterations, cells).
-template <int D>
-__global__ void __launch_bounds__(MLP_BLOCK) k_fields_mlp(Grid g, Phys<float> ph, Fields<float> fl, const float *P,
-                                                         const uint16_t *W2b, const float *norm, float tol,
-                                                         unsigned long long *counters) {
-    const int tid = threadIdx.x;
-    int x = blockIdx.x * MLP_BLOCK + tid, y = blockIdx.y, z = blockIdx.z;
-    const bool active = x < g.nx;
-    if (!active) x = g.nx - 1;
-    const long long c = cell_index<D>(g, x, y, z);
-    float rho = fl.rho[c];
-    float inv_rho = 1.0f / rho;
-    float u[3], F[3], uF = 0, u2 = 0;
-    for (int a = 0; a < D; a++) {
-        float dl = 0.5f * (fl.lap[nb_axis<D>(g, x, y, z, a, 1)] - fl.lap[nb_axis<D>(g, x, y, z, a, -1)]);
-        F[a] = ph.kappa * rho * dl;
-        u[a] = (fl.J[a * g.N + c] + 0.5f * F[a]) * inv_rho;
-        uF += u[a] * F[a];
-        u2 += u[a] * u[a];
-    }
-    float E = (fl.G[c] + 0.5f * uF) * inv_rho;
-    float e = E - 0.5f * u2;
-    float x0, x1, yh[1];
-    normalise(norm, rho, e, x0, x1);
-    forward_wave<1>(x0, x1, net_of(P, W2b), yh);
-    // The residual check validates the temperature only, so the pressure and
-    // c_s^2 of the step come from the equation of state at the accepted T
-    // (explicit once T is known); the network's P and c_s^2 outputs are
-    // trained and reported but not used here.
-    float T = yh[0] * norm[5] + norm[4];
-    float Pr, c2;
-    bool fb;
-    if (ph.pr) {
-        const double rd = (double)rho, ed = (double)e;
-        EosPoint q = pr_eos(ph, rd, (double)T);
-        fb = !(fabs(q.e - ed) <= (double)tol * q.cv * fabs((double)T));
-        int it = 0;
-        if (fb) {
-            const double Td = pr_temperature(ph, rd, ed, (double)T, it);
-            q = pr_eos(ph, rd, Td);
-            T = (float)Td;
+// Per-cell passes with the surrogate.  T comes from the network; a cell whose
+// caloric residual |e(rho, T_hat) - e| / (c_v T_hat) exceeds tol (or is not
+// finite) takes one FP64 Newton step on e(rho, T) = e from T_hat -- exact for
+// van der Waals, whose e is linear in T; with the Peng-Robinson equation of
+// state the residual is taken with e(rho, T_hat) and c_v(rho, T_hat) in FP64,
+// and a failing cell runs Newton's method from T_hat to convergence.  The
+// residual check validates the temperature only, so P and c_s^2 come from the
+// equation of state at the accepted T (explicit once T is known); the network's
+// P and c_s^2 outputs are trained and reported but not used here.
+//   MLP_STEP    the fields of the multi-kernel step, counters kept
+//   MLP_EXPORT  rho, u, T, P to the caller's arrays
+//   MLP_SUMS    the conservation partials
+// A workgroup keeps the network in LDS and takes runs of 256-cell units as the
+// explicit read-back does (512^3 cells: 3.4 ms; with the parameters read from
+// global memory by every wavefront 9.4 ms for the fields, and 1.6 ms more to
+// export them).  Bound by the vector ALU.
+enum { MLP_STEP, MLP_EXPORT, MLP_SUMS };
+template <int D, int MODE>
+__global__ void __launch_bounds__(BX, 2) k_cells_mlp(Grid g, Phys<float> ph, MomSrc<float> m, Fields<float> fl,
+                                                  const float *__restrict__ Pn, const float *__restrict__ norm,
+                                                  float tol, unsigned long long *counters, ReadOut o) {
+    __shared__ __attribute__((aligned(16))) NetLds<1, false> net;
+    net_to_lds(net, Pn, threadIdx.x, BX);
+    __syncthreads();
+    double acc[RED_VALS] = {0, 0, 0, 0, 0, 0, 0};
+    unsigned n_fb = 0, n_cell = 0, n_it = 0;
+    long long u0, u1;
+    unsigned per_plane;
+    read_units(g, u0, u1, per_plane);
+    for (long long un = u0; un < u1; un++) {
+        const int z = (int)((unsigned long long)un / per_plane);
+        const unsigned p = (unsigned)(un - (long long)z * per_plane) * BX + threadIdx.x;
+        int y = (int)(p / (unsigned)g.nx), x = (int)(p - (unsigned)y * (unsigned)g.nx);
+        const bool active = y < g.ny;  // other lanes evaluate the plane's last cell and write nothing
+        if (!active) {
+            x = g.nx - 1;
+            y = g.ny - 1;
         }
-        fl.e[c] = (float)pr_eos(ph, rd, (double)T).e;
-        Pr = (float)q.P;
-        c2 = (float)q.cs2;
-        if (counters) {
-            unsigned long long *slot = counter_slot(counters);
-            wave_count(&slot[2], active ? (unsigned)it : 0u);
-            wave_count(&slot[3], active ? 1u : 0u);
+        const long long c = cell_index<D>(g, x, y, z);
+        const CellKin<float> k = cell_kin<D>(g, ph, m, fl.lap, x, y, z);
+        const float rho = k.rho, e = k.e;
+        float x0[1], x1[1], yh[1][1];
+        normalise(norm, rho, e, x0[0], x1[0]);
+        forward_tiles<1, false, 2>(x0, x1, net, yh);
+        float T = yh[0][0] * norm[5] + norm[4];
+        float Pr, c2, ec = 0.0f;
+        bool fb;
+        if (ph.pr) {
+            const double rd = (double)rho, ed = (double)e;
+            EosPoint q = pr_eos(ph, rd, (double)T);
+            fb = !(fabs(q.e - ed) <= (double)tol * q.cv * fabs((double)T));
+            if (fb) {
+                int it = 0;
+                const double Td = pr_temperature(ph, rd, ed, (double)T, it);
+                q = pr_eos(ph, rd, Td);
+                T = (float)Td;
+                n_it += active ? (unsigned)it : 0u;
+            }
+            if (MODE == MLP_STEP) ec = (float)pr_eos(ph, rd, (double)T).e;
+            Pr = (float)q.P;
+            c2 = (float)q.cs2;
+        } else {
+            float r = fabsf(ph.cv * T - ph.a * rho - e) / (ph.cv * fabsf(T));
+            fb = !(r <= tol);
+            if (fb) {
+                double Td = (double)T, rd = (double)rho, cv = (double)ph.cv, a = (double)ph.a;
+                Td = Td - (cv * Td - a * rd - (double)e) / cv;  // Newton on e(rho, T) - e = 0
+                double omb = 1.0 - (double)ph.b * rd;
+                T = (float)Td;
+                Pr = (float)(rd * (double)ph.R * Td / omb - a * rd * rd);
+                c2 = (float)((double)ph.R * Td * (1.0 + (double)ph.R / cv) / (omb * omb) - 2.0 * a * rd);
+            } else {
+                Pr = vdw_pressure(ph, rho, T);
+                c2 = vdw_cs2(ph, rho, T);
+            }
         }
-    } else {
-    float r = fabsf(ph.cv * T - ph.a * rho - e) / (ph.cv * fabsf(T));
-    fb = !(r <= tol);
-    if (fb) {
-        double Td = (double)T, rd = (double)rho, cv = (double)ph.cv, a = (double)ph.a;
-        Td = Td - (cv * Td - a * rd - (double)e) / cv;  // Newton on e(rho, T) - e = 0
-        double omb = 1.0 - (double)ph.b * rd;
-        T = (float)Td;
-        Pr = (float)(rd * (double)ph.R * Td / omb - a * rd * rd);
-        c2 = (float)((double)ph.R * Td * (1.0 + (double)ph.R / cv) / (omb * omb) - 2.0 * a * rd);
-    } else {
-        Pr = vdw_pressure(ph, rho, T);
-        c2 = vdw_cs2(ph, rho, T);
+        n_fb += fb && active ? 1u : 0u;
+        n_cell += active ? 1u : 0u;
+        if (!active) continue;
+        if constexpr (MODE == MLP_STEP) {
+            float theta = Pr * k.inv_rho;
+            for (int a = 0; a < D; a++) {
+                fl.u[a * g.N + c] = k.u[a];
+                fl.F[a * g.N + c] = k.F[a];
+                fl.Lam[a * g.N + c] = rho * k.u[a] * (k.u[a] * k.u[a] + 3.0f * (theta - 1.0f / 3.0f));
+            }
+            fl.T[c] = T;
+            fl.P[c] = Pr;
+            fl.h[c] = e + theta;
+            fl.cs2[c] = c2;
+            if (ph.pr) fl.e[c] = ec;
+        } else {
+            read_cell<D, float, MODE == MLP_SUMS>(g, k, T, Pr, c, (double)ph.b, o, acc);
+        }
     }
-    }
-    unsigned long long nfb = __popcll(__ballot(fb && active));
-    unsigned long long nact = __popcll(__ballot(active));
-    if ((tid & 63) == 0 && counters) {
+    if constexpr (MODE == MLP_STEP) {
         unsigned long long *slot = counter_slot(counters);
-        atomicAdd(&slot[0], nfb);
-        atomicAdd(&slot[1], nact);
+        wave_count(&slot[0], n_fb);
+        wave_count(&slot[1], n_cell);
+        if (ph.pr) {
+            wave_count(&slot[2], n_it);
+            wave_count(&slot[3], n_cell);
+        }
     }
-    if (!active) return;
-    float theta = Pr * inv_rho;
-    for (int a = 0; a < D; a++) {
-        fl.u[a * g.N + c] = u[a];
-        fl.F[a * g.N + c] = F[a];
-        fl.Lam[a * g.N + c] = rho * u[a] * (u[a] * u[a] + 3.0f * (theta - 1.0f / 3.0f));
-    }
-    fl.T[c] = T;
-    fl.P[c] = Pr;
-    fl.h[c] = e + theta;
-    fl.cs2[c] = c2;
+    if constexpr (MODE == MLP_SUMS) block_partials(acc, o.partials);
 }
 
 // ---------------------------------------------------------------------------
@@ -444,33 +445,54 @@ __global__ void k_normalise_samples(int n, const float *x, const double *t, cons
 }  // namespace lbm
 
 // ---------------------------------------------------------------------------
-template <int D, class C> int launch_fields_mlp(lbm_ctx *c, Fields<C> fl, bool count) {
+static Phys<float> make_phys_f32(const lbm_params &p) {
+    Phys<float> ph;
+    ph.a = (float)p.a; ph.b = (float)p.b; ph.R = (float)p.R; ph.cv = (float)p.cv;
+    ph.mu = (float)p.mu; ph.eta = (float)p.eta; ph.k = (float)p.k; ph.kappa = (float)p.kappa;
+    ph.inv_cv = (float)(1.0 / p.cv); ph.k_over_mu = (float)(p.k / p.mu); ph.eta_over_mu = (float)(p.eta / p.mu);
+    ph.sgn_eps = (float)p.upwind_eps;
+    ph.sc_cmu = (float)p.sc_cmu; ph.sc_ceta = (float)p.sc_ceta; ph.sc_ck = (float)p.sc_ck;
+    ph.pr = lbm_eos_is_pr(p.eos) ? 1 : 0;
+    ph.pr_m = p.pr_m; ph.pr_Tc = p.pr_Tc; ph.pr_c0 = p.pr_c0; ph.pr_c1 = p.pr_c1;
+    return ph;
+}
+template <int D, int MODE>
+static int launch_cells_mlp(lbm_ctx *c, const MomSrc<float> &m, const Fields<float> &fl, const ReadOut &o) {
+    hipLaunchKernelGGL((mlp::k_cells_mlp<D, MODE>), dim3(READ_BLOCKS), dim3(BX), 0, c->stream, c->grid,
+                       make_phys_f32(c->p), m, fl, c->mlp_params, c->mlp_norm, (float)c->p.mlp_tol, c->mlp_counters, o);
+    return lbm_note(hipGetLastError());
+}
+template <int D, class C> int launch_fields_mlp(lbm_ctx *c, Fields<C> fl) {
     if constexpr (!std::is_same<C, float>::value) {
         (void)c;
         (void)fl;
-        (void)count;
         return LBM_EINVAL;
     } else {
-        Phys<float> ph;
-        const lbm_params &p = c->p;
-        ph.a = (float)p.a; ph.b = (float)p.b; ph.R = (float)p.R; ph.cv = (float)p.cv;
-        ph.mu = (float)p.mu; ph.eta = (float)p.eta; ph.k = (float)p.k; ph.kappa = (float)p.kappa;
-        ph.inv_cv = (float)(1.0 / p.cv); ph.k_over_mu = (float)(p.k / p.mu); ph.eta_over_mu = (float)(p.eta / p.mu);
-        ph.sgn_eps = (float)p.upwind_eps;
-        ph.sc_cmu = (float)p.sc_cmu; ph.sc_ceta = (float)p.sc_ceta; ph.sc_ck = (float)p.sc_ck;
-        ph.pr = lbm_eos_is_pr(p.eos) ? 1 : 0;
-        ph.pr_m = p.pr_m; ph.pr_Tc = p.pr_Tc; ph.pr_c0 = p.pr_c0; ph.pr_c1 = p.pr_c1;
-        dim3 gr((unsigned)((p.nx + mlp::MLP_BLOCK - 1) / mlp::MLP_BLOCK), (unsigned)p.ny, (unsigned)p.nz);
-        hipLaunchKernelGGL((mlp::k_fields_mlp<D>), gr, dim3(mlp::MLP_BLOCK), 0, c->stream, c->grid, ph, fl, c->mlp_params,
-                           c->mlp_w2b, c->mlp_norm, (float)p.mlp_tol,
-                           count ? c->mlp_counters : (unsigned long long *)nullptr);
-        return lbm_note(hipGetLastError());
+        const MomSrc<C> m{fl.rho, (long long)c->p.nx * c->p.ny, (long long)c->grid.N, D + 1};
+        return launch_cells_mlp<D, mlp::MLP_STEP>(c, m, fl, ReadOut{});
     }
 }
-template int launch_fields_mlp<2, float>(lbm_ctx *, Fields<float>, bool);
-template int launch_fields_mlp<3, float>(lbm_ctx *, Fields<float>, bool);
-template int launch_fields_mlp<2, double>(lbm_ctx *, Fields<double>, bool);
-template int launch_fields_mlp<3, double>(lbm_ctx *, Fields<double>, bool);
+template <int D, class C>
+int launch_readback_mlp(lbm_ctx *c, const MomSrc<C> &m, Fields<C> fl, const ReadOut &o) {
+    if constexpr (!std::is_same<C, float>::value) {
+        (void)c;
+        (void)m;
+        (void)fl;
+        (void)o;
+        return LBM_EINVAL;
+    } else {
+        return o.partials ? launch_cells_mlp<D, mlp::MLP_SUMS>(c, m, fl, o)
+                          : launch_cells_mlp<D, mlp::MLP_EXPORT>(c, m, fl, o);
+    }
+}
+#define INSTANTIATE(D, C)                                     \
+    template int launch_fields_mlp<D, C>(lbm_ctx *, Fields<C>); \
+    template int launch_readback_mlp<D, C>(lbm_ctx *, const MomSrc<C> &, Fields<C>, const ReadOut &);
+INSTANTIATE(2, float)
+INSTANTIATE(3, float)
+INSTANTIATE(2, double)
+INSTANTIATE(3, double)
+#undef INSTANTIATE
 
 // ---------------------------------------------------------------------------
 // Scratch of lbm_mlp_loss_grad_noalloc: the per-block gradient partials (NP
@@ -526,13 +548,23 @@ int lbm_mlp_forward(const float *params, const float *norm, const float *x, floa
         return LBM_EINVAL;
     if (B == 0) return LBM_OK;
     if (!params || !norm || !x || !y) return LBM_EINVAL;
-    dim3 gr((unsigned)((B + 63) / 64));
+    hipStream_t s = (hipStream_t)stream;
+    // workgroups of 4 x 32 NT samples
+    auto grid = [&](int nt) {
+        const long long n = ((long long)B + 128 * nt - 1) / (128 * nt);
+        return dim3((unsigned)std::min<long long>(n, mlp::FWD_BLOCKS));
+    };
+    const bool wide = B >= 256 * 512;
     if (precision == LBM_MLP_BF16_L1)
-        hipLaunchKernelGGL(mlp::k_forward_l1mfma, gr, dim3(64), 0, (hipStream_t)stream, params, norm, x, y, B);
+        hipLaunchKernelGGL(mlp::k_forward_l1mfma, grid(2), dim3(256), 0, s, params, norm, x, y, B);
+    else if (precision == LBM_MLP_BF16 && wide)
+        hipLaunchKernelGGL((mlp::k_forward<false, 4>), grid(4), dim3(256), 0, s, params, norm, x, y, B);
     else if (precision == LBM_MLP_BF16)
-        hipLaunchKernelGGL(mlp::k_forward<true>, gr, dim3(64), 0, (hipStream_t)stream, params, norm, x, y, B);
+        hipLaunchKernelGGL((mlp::k_forward<false, 2>), grid(2), dim3(256), 0, s, params, norm, x, y, B);
+    else if (wide)
+        hipLaunchKernelGGL((mlp::k_forward<true, 4>), grid(4), dim3(256), 0, s, params, norm, x, y, B);
     else
-        hipLaunchKernelGGL(mlp::k_forward<false>, gr, dim3(64), 0, (hipStream_t)stream, params, norm, x, y, B);
+        hipLaunchKernelGGL((mlp::k_forward<true, 2>), grid(2), dim3(256), 0, s, params, norm, x, y, B);
     return lbm_note(hipGetLastError());
 }
 

@@ -1,5 +1,4 @@
-// Wave-level inference of the 2 -> 64 -> 64 -> 3 equation-of-state surrogate
-// without LDS.  One wavefront evaluates 64 samples (one per lane).
+// Wave-level inference of the 2 -> 64 -> 64 -> 3 equation-of-state surrogate.
 //
 // The hidden layer is computed transposed, Z2^T = W2 H1^T, with
 // v_mfma_f32_32x32x16_bf16: A = W2 (rows: output neurons, loaded as 8
@@ -11,6 +10,8 @@
 // samples; the output layer is a per-lane partial dot product completed with
 // the partner lane l ^ 32.
 #pragma once
+
+#include <type_traits>
 
 #include "lbm_device.hpp"
 
@@ -45,97 +46,141 @@ __device__ __forceinline__ void normalise(const float *norm, float rho, float e,
     x1 = 2.0f * (e - norm[2]) / (norm[3] - norm[2]) - 1.0f;
 }
 
-// Parameter pointers of one forward pass: the small layers may live in LDS,
-// the 64 x 64 hidden weights are read as BF16 (w2b, rows of w2_ld elements,
-// global memory or LDS) or rounded on the fly from FP32 (w2b null: w2).
+// Parameter pointers of one forward pass with both hidden layers on MFMA
 struct Net {
-    const float *w1, *b1;  // [64][2], [64]
-    const uint16_t *w2b;   // [64][w2_ld] BF16, row-major [out][in], or null
-    const float *w2;       // [64][64] FP32 (when w2b is null)
+    const uint16_t *w2b;        // [64][w2_ld] BF16, row-major [out][in]
     const float *b2, *w3, *b3;  // [64], [NOUT][64], [NOUT]
     int w2_ld;
 };
-__device__ __forceinline__ Net net_of(const float *P, const uint16_t *W2b) {
-    return Net{P + OFF_W1, P + OFF_B1, W2b, P + OFF_W2, P + OFF_B2, P + OFF_W3, P + OFF_B3, H};
-}
 
-// Returns the normalised outputs 0..NOUT-1 of this lane's sample.  Every lane
-// of the wavefront must call with uniform control flow.  The 32-sample halves
-// of the wavefront go through the hidden layer one after the other and each
-// k-step's B operand is formed just before its MFMA, which keeps the live
-// registers low.  HALVES = 1 evaluates only the samples of lanes 0..31 (the
-// outputs of lanes 32..63 are left unset).
-template <int NOUT, int HALVES = 2>
-__device__ __forceinline__ void forward_wave(float x0, float x1, const Net &p, float y[NOUT]) {
-    static_assert(HALVES == 1 || HALVES == 2, "one or two 32-sample halves");
-    const int lane = threadIdx.x & 63;
-    const int hh = lane >> 5, c = lane & 31;
-    // byte offset of this lane's A-operand row segment in the BF16 weights
-    // (uniform base + 32-bit lane offset + constant per (mt, ks))
-    const unsigned a_off = (unsigned)(c * p.w2_ld + 8 * hh) * 2u;
+// ---------------------------------------------------------------------------
+// Stand-alone form: first layer on the vector ALU in FP32, hidden layer on
+// BF16 MFMA or (F32) on the FP32 matrix instruction.  The small layers and the
+// hidden weights sit in LDS, written once per workgroup, and one read of a
+// weight serves NT tiles of 32 samples: what bounds it is the vector ALU (per
+// tile 112 instructions in the first layer, 32 (1 + NOUT) in the last), not the
+// parameter reads that a pass of one tile spends its time on (1,000,003 samples,
+// three outputs: 113 us with one wavefront per workgroup converting W2 for
+// itself, 29 us so).
+template <int NOUT, bool F32> struct NetLds {
+    static constexpr int W2LD = F32 ? 68 : 72;  // padded rows: conflict-free 16-byte reads
+    // first layer by input position: BF16 position k is neuron k; F32 position
+    // 32 h + s is neuron 2 s + h (the matrix instruction's k index of step s in
+    // lane half h), and W2's columns follow the same order
+    float w1x[H], w1y[H], b1[H], b2[H], w3[NOUT][H], b3[4];
+    typename std::conditional<F32, float, uint16_t>::type w2[H * W2LD];
+};
+template <int NOUT, bool F32>
+__device__ __forceinline__ void net_to_lds(NetLds<NOUT, F32> &n, const float *__restrict__ P, int tid, int nt) {
+    for (int k = tid; k < H; k += nt) {
+        const int q = F32 ? 2 * (k & 31) + (k >> 5) : k;
+        n.w1x[k] = P[OFF_W1 + 2 * q];
+        n.w1y[k] = P[OFF_W1 + 2 * q + 1];
+        n.b1[k] = P[OFF_B1 + q];
+        n.b2[k] = P[OFF_B2 + k];
+        for (int o = 0; o < NOUT; o++) n.w3[o][k] = P[OFF_W3 + o * H + k];
+    }
+    if (tid < NOUT) n.b3[tid] = P[OFF_B3 + tid];
+    for (int r = tid; r < H * H; r += nt) {
+        const int m = r / H, q = r % H;
+        const float v = P[OFF_W2 + r];
+        if constexpr (F32) n.w2[m * n.W2LD + 32 * (q & 1) + (q >> 1)] = v;
+        else n.w2[m * n.W2LD + q] = bf16_hw(v);
+    }
+}
+// Normalised outputs of 32 NT samples: lane l holds samples 64 p + l, p < NT / 2.
+// Uniform control flow over the wavefront.
+template <int NOUT, bool F32, int NT>
+__device__ __forceinline__ void forward_tiles(const float (&x0)[NT / 2], const float (&x1)[NT / 2],
+                                              const NetLds<NOUT, F32> &n, float (&y)[NT / 2][NOUT]) {
+    const int lane = threadIdx.x & 63, hh = lane >> 5, c = lane & 31;
+    float xs0[NT], xs1[NT];
 #pragma unroll
-    for (int nt = 0; nt < HALVES; nt++) {
-        // inputs of the sample this lane serves in the B operand
-        const float xs0 = __shfl(x0, 32 * nt + c, 64), xs1 = __shfl(x1, 32 * nt + c, 64);
-        f32x16 acc[2];
+    for (int t = 0; t < NT; t++) {
+        xs0[t] = __shfl(x0[t / 2], 32 * (t & 1) + c, 64);
+        xs1[t] = __shfl(x1[t / 2], 32 * (t & 1) + c, 64);
+    }
+    // accumulators seeded with b2 of their neurons 32 mt + 8 (v / 4) + 4 hh + v % 4
+    f32x16 acc[NT][2], seed[2];
 #pragma unroll
-        for (int mt = 0; mt < 2; mt++)
+    for (int mt = 0; mt < 2; mt++)
 #pragma unroll
-            for (int v = 0; v < 16; v++) acc[mt][v] = 0.0f;
+        for (int q = 0; q < 4; q++) {
+            const float4 b = *(const float4 *)&n.b2[32 * mt + 8 * q + 4 * hh];
+            seed[mt][4 * q] = b.x;
+            seed[mt][4 * q + 1] = b.y;
+            seed[mt][4 * q + 2] = b.z;
+            seed[mt][4 * q + 3] = b.w;
+        }
 #pragma unroll
-        for (int ks = 0; ks < 4; ks++) {
-            float hv[8];
+    for (int ks = 0; ks < (F32 ? 8 : 4); ks++) {
+        // input positions of this lane half in this group: 8 of a BF16 k-step,
+        // or those of four FP32 k-steps
+        constexpr int G = F32 ? 4 : 8;
+        const int k0 = F32 ? 32 * hh + 4 * ks : 16 * ks + 8 * hh;
+        float wx[G], wy[G], b[G];
 #pragma unroll
-            for (int j = 0; j < 8; j++) {
-                const int k = 16 * ks + 8 * hh + j;
-                hv[j] = relu(fmaf(p.w1[2 * k], xs0, fmaf(p.w1[2 * k + 1], xs1, p.b1[k])));
-            }
-            // two activations per convert
-            uint4 bp;
-            bp.x = bf16x2_hw(hv[0], hv[1]);
-            bp.y = bf16x2_hw(hv[2], hv[3]);
-            bp.z = bf16x2_hw(hv[4], hv[5]);
-            bp.w = bf16x2_hw(hv[6], hv[7]);
-            const bf16x8 b = __builtin_bit_cast(bf16x8, bp);
+        for (int j = 0; j < G; j += 4) {
+            *(float4 *)&wx[j] = *(const float4 *)&n.w1x[k0 + j];
+            *(float4 *)&wy[j] = *(const float4 *)&n.w1y[k0 + j];
+            *(float4 *)&b[j] = *(const float4 *)&n.b1[k0 + j];
+        }
+        const uint4 a0 = *(const uint4 *)&n.w2[c * n.W2LD + k0], a1 = *(const uint4 *)&n.w2[(32 + c) * n.W2LD + k0];
 #pragma unroll
-            for (int mt = 0; mt < 2; mt++) {
-                bf16x8 a;
-                if (p.w2b) {
-                    const uint4 raw =
-                        *(const uint4 *)((const char *)p.w2b + a_off + (unsigned)((32 * mt * p.w2_ld + 16 * ks) * 2));
-                    a = __builtin_bit_cast(bf16x8, raw);
-                } else {
-                    const float *row = p.w2 + (32 * mt + c) * H + 16 * ks + 8 * hh;
+        for (int t = 0; t < NT; t++) {
+            float hv[G];
 #pragma unroll
-                    for (int j = 0; j < 8; j++) a[j] = to_bf16(row[j]);
+            for (int j = 0; j < G; j++) hv[j] = relu(fmaf(wx[j], xs0[t], fmaf(wy[j], xs1[t], b[j])));
+            if constexpr (F32) {
+                const float *w0 = (const float *)&a0, *w1 = (const float *)&a1;
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const bool first = ks == 0 && j == 0;
+                    acc[t][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(w0[j], hv[j], first ? seed[0] : acc[t][0], 0, 0, 0);
+                    acc[t][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(w1[j], hv[j], first ? seed[1] : acc[t][1], 0, 0, 0);
                 }
-                acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[mt], 0, 0, 0);
+            } else {
+                const uint4 bp = {bf16x2_hw(hv[0], hv[1]), bf16x2_hw(hv[2], hv[3]), bf16x2_hw(hv[4], hv[5]),
+                                  bf16x2_hw(hv[6], hv[7])};
+                const bf16x8 bv = __builtin_bit_cast(bf16x8, bp);
+                acc[t][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a0), bv,
+                                                                   ks == 0 ? seed[0] : acc[t][0], 0, 0, 0);
+                acc[t][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a1), bv,
+                                                                   ks == 0 ? seed[1] : acc[t][1], 0, 0, 0);
             }
-            // keep the next k-step's parameter loads from being hoisted here:
-            // bounds the live registers of the first layer to one k-step
-            __builtin_amdgcn_sched_barrier(0);
         }
-        float ys[NOUT];
+        // bounds the live registers to one group's parameters
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    float ys[NT][NOUT];
 #pragma unroll
-        for (int k = 0; k < NOUT; k++) ys[k] = 0.0f;
+    for (int t = 0; t < NT; t++)
 #pragma unroll
-        for (int mt = 0; mt < 2; mt++) {
+        for (int k = 0; k < NOUT; k++) ys[t][k] = 0.0f;
 #pragma unroll
-            for (int v = 0; v < 16; v++) {
-                const int o = 32 * mt + 8 * (v >> 2) + 4 * hh + (v & 3);
-                const float h2 = relu(acc[mt][v] + p.b2[o]);
+    for (int mt = 0; mt < 2; mt++)
 #pragma unroll
-                for (int k = 0; k < NOUT; k++) ys[k] = fmaf(p.w3[k * H + o], h2, ys[k]);
-            }
-            __builtin_amdgcn_sched_barrier(0);
+        for (int q = 0; q < 4; q++) {
+            float w[NOUT][4];
+#pragma unroll
+            for (int k = 0; k < NOUT; k++) *(float4 *)w[k] = *(const float4 *)&n.w3[k][32 * mt + 8 * q + 4 * hh];
+#pragma unroll
+            for (int t = 0; t < NT; t++)
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const float h2 = relu(acc[t][mt][4 * q + r]);
+#pragma unroll
+                    for (int k = 0; k < NOUT; k++) ys[t][k] = fmaf(w[k][r], h2, ys[t][k]);
+                }
         }
+#pragma unroll
+    for (int t = 0; t < NT; t++)
 #pragma unroll
         for (int k = 0; k < NOUT; k++) {
-            ys[k] += __shfl_xor(ys[k], 32, 64);
-            // lane l's own sample is 32 nt + c with nt = l / 32
-            if (hh == nt) y[k] = ys[k] + p.b3[k];
+            ys[t][k] += __shfl_xor(ys[t][k], 32, 64);
+            // lane l's sample of pair p sits in tile 2 p + l / 32
+            if (hh == (t & 1)) y[t / 2][k] = ys[t][k] + n.b3[k];
         }
-    }
 }
 
 // ---------------------------------------------------------------------------

@@ -89,11 +89,11 @@ template <class C> __device__ __forceinline__ AxisEq<C> axis_eq(C u, C theta) {
 template <int D, class S>
 __global__ void __launch_bounds__(BX) k_init(Grid g, Phys<double> ph, RefPops ref, const double *__restrict__ rho,
                                              const double *__restrict__ u, const double *__restrict__ T,
-                                             typename S::T *__restrict__ fo, typename S::T *__restrict__ go) {
+                                             typename S::T *__restrict__ fo) {
     using C = typename S::C;
     constexpr int Q = Lattice<D>::Q;
-    int x = blockIdx.x * BX + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-    if (x >= g.nx) return;
+    int x, y, z;
+    if (!flat_cell(g, x, y, z)) return;
     long long c = cell_index<D>(g, x, y, z);
     double r = rho[c], t = T[c];
     double P, e;
@@ -123,9 +123,8 @@ __global__ void __launch_bounds__(BX) k_init(Grid g, Phys<double> ph, RefPops re
             gsum = (qx * py + px * qy) * pz + px * py * qz;
         }
         double geq = feq * eps + 0.5 * r * gsum;
-        const long long pi = pop_index<Q>(g, i, z, x + (long long)g.nx * y);
-        fo[pi] = S::enc((C)feq, (C)ref.f[i]);
-        go[pi] = S::enc((C)geq, (C)ref.g[i]);
+        store_pair(fo, pop_index<Q>(g, i, z, x + (long long)g.nx * y), S::enc((C)feq, (C)ref.f[i]),
+                   S::enc((C)geq, (C)ref.g[i]));
     }
 }
 

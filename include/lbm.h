@@ -210,8 +210,9 @@ int lbm_synchronize(lbm_ctx *ctx);
  * stream with HIP events around every kernel launch and writes the average
  * duration in milliseconds of each kernel kind of the step to host_ms[k],
  * k < LBM_NUM_KERNELS (names from lbm_kernel_name; unused slots get "" and
- * 0).  Blocking.  Errors: as lbm_step; LBM_EINVAL when nslots <
- * LBM_NUM_KERNELS. */
+ * 0); of a kernel that takes several steps in one launch (small D2Q9
+ * lattices, "k_block2d"), its duration per step.  Blocking.  Errors: as
+ * lbm_step; LBM_EINVAL when nslots < LBM_NUM_KERNELS. */
 #define LBM_NUM_KERNELS 4
 int lbm_step_timed(lbm_ctx *ctx, int n, double *host_ms, int nslots);
 const char *lbm_kernel_name(const lbm_ctx *ctx, int kernel);
@@ -222,8 +223,11 @@ const char *lbm_kernel_name(const lbm_ctx *ctx, int kernel);
  * followed by the small pass completing its moment side channel (kernel kinds
  * "k_fused", "k_fused_fixup"; with the surrogate EOS the network runs in a
  * pass ahead of them, kind "k_eos_surrogate", writing the network's T of
- * every cell and whether it passed the residual check), 0 when
- * it runs the four-kernel path (moments, Laplacian, fields, collide). */
+ * every cell and whether it passed the residual check; small D2Q9 lattices
+ * with the explicit EOS and FP32 or FP64 storage take several steps in one
+ * launch instead, kind "k_block2d"), 0 when it runs the four-kernel path
+ * (moments, Laplacian, fields, collide; with x walls on a small D2Q9 lattice
+ * "k_block2d" in its place). */
 int lbm_is_fused(const lbm_ctx *ctx);
 
 /* Algorithmic HBM bytes moved per cell update by lbm_step (2 Q populations

@@ -11,6 +11,7 @@
 
 #include "lbm.h"
 #include "lbm_internal.hpp"
+#include "lbm_block2d.hpp"
 #include <algorithm>
 #include <type_traits>
 
@@ -228,7 +229,7 @@ template <int D, class S> struct Impl {
     static int fused_prepare(lbm_ctx *c) { return mlp(c) ? fused_prepare_t<true>(c) : fused_prepare_t<false>(c); }
     template <bool M> static int fused_prepare_t(lbm_ctx *c) {
         using TL = TileOf<S, M>;
-        if (!c->fused) return LBM_OK;
+        if (!c->fused || c->b2_threads) return LBM_OK;
         for (int s = 0; s < 2; s++)
             if (hipMemsetAsync(c->IN[s], 0, c->in_bytes, c->stream) != hipSuccess)
                 return lbm_note(hipGetLastError());
@@ -455,7 +456,7 @@ template <int D, class S> struct Impl {
     // k_moments reads, 5.1 ms at 512^3 cells in BF16); where the next step would
     // complete them on load, k_complete does so into the field arrays (1.5 ms).
     static MomSrc<C> state_moments(lbm_ctx *c) {
-        if (!c->fused) {
+        if (!c->fused || c->b2_threads) {
             moments_launch(c);
             return field_moments(c);
         }
@@ -515,14 +516,18 @@ template <int D, class S> struct Impl {
         *fS = fl.sc[src];
         *fs = fl.sc[src + 1];
     }
-    // collide into buffer nxt (multi-kernel path): the post-collision set, or
-    // with x walls the arrived one and then what the wall ghosts emit
-    static void collide_launch(lbm_ctx *c, Fields<C> fl, const C *fS, const C *fs, int nxt) {
+    static Walls walls(const lbm_ctx *c) {
         Walls w;
         for (int s = 0; s < 2; s++) {
             for (int a = 0; a < 3; a++) w.u[s][a] = c->p.wall_u[s][a];
             w.T[s] = c->p.wall_T[s];
         }
+        return w;
+    }
+    // collide into buffer nxt (multi-kernel path): the post-collision set, or
+    // with x walls the arrived one and then what the wall ghosts emit
+    static void collide_launch(lbm_ctx *c, Fields<C> fl, const C *fS, const C *fs, int nxt) {
+        const Walls w = walls(c);
         if (c->grid.wallx)
             hipLaunchKernelGGL((k_collide<D, S, true>), flat_grid(c), dim3(BX), 0, c->stream, c->grid,
                                make_phys<C>(c->p), c->ref, (const T *)c->f[c->cur], fl, (T *)c->f[nxt], fS, fs, w,
@@ -537,7 +542,94 @@ template <int D, class S> struct Impl {
                                dim3(64), 0, c->stream, c->grid, make_phys<C>(c->p), c->ref, w, fl,
                                (const C *)c->ghost, (T *)c->f[nxt], (T *)c->g[nxt]);
     }
+    // Whether and how small D2Q9 lattices take several steps in one launch.  A
+    // region has at most 1024 cells (FP32; 128 registers per thread) or 512
+    // (FP64, x walls).  The whole lattice where it fits (us per step, FP64 and
+    // FP32: 64 x 4 cells 1.6 and 1.3, fused 8.8 and 8.9; with x walls 2.6 and
+    // 2.4, multi-kernel 20); else all rows of `own` columns and a halo of 4 per
+    // step, by the shortest time per step of the model below (4 us per launch,
+    // then a step's latency, which grows with the wavefronts per SIMD: fitted to
+    // those and 512 x 4 2.1 and 1.8, 1000 x 4 2.2 and 1.9, 400 x 16 3.7 and 3.1,
+    // 800 x 32 FP32 5.1), where it is shorter than a step of the other path
+    // (fused 10 us, multi-kernel with x walls 20, on any of these).  Beyond 64
+    // (32) rows not even one step's region fits.
+    static void block2d_plan(lbm_ctx *c) {
+        c->b2_threads = 0;
+        const bool wide = std::is_same<C, double>::value;
+        if (D != 2 || sizeof(T) == 2 || c->p.eos != LBM_EOS_VDW || c->sc || (!c->fused && !c->grid.wallx)) return;
+        const int cap = wide || c->grid.wallx ? 512 : 1024, nx = c->p.nx, ny = c->p.ny;
+        auto plan = [&](int threads, int own, int halo, int steps) {
+            c->b2_threads = threads;
+            c->b2_own = own;
+            c->b2_halo = halo;
+            c->b2_steps = steps;
+        };
+        if ((long long)nx * ny <= cap) return plan(nx * ny, nx, 0, 1024);
+        if (ny > cap / 16) return;
+        const double launch = 4.0, base = wide ? 1.0 : 0.95, per = wide ? 0.65 : 0.45;
+        double best = c->grid.wallx ? 16.0 : 8.0;
+        for (int k = 1; k <= 16; k++)
+            for (int own = 4; (own + 8 * k) * ny <= cap; own += 4) {
+                const int threads = (own + 8 * k) * ny;
+                const double rounds = std::ceil(((nx + own - 1) / own) / 256.0);
+                const double t = rounds * (launch / k + base + per * ((threads + 255) / 256));
+                if (t >= best) continue;
+                best = t;
+                plan(threads, own, 4 * k, k);
+            }
+    }
+    template <bool WALL, int NT> static void block2d_run(lbm_ctx *c, int steps) {
+        if constexpr (D == 2 && sizeof(T) != 2) {
+            Block2DArgs<C, T> a;
+            a.g = c->grid;
+            a.ph = make_phys<C>(c->p);
+            a.ref = c->ref;
+            a.w = walls(c);
+            a.own = c->b2_own;
+            a.halo = c->b2_halo;
+            a.steps = steps;
+            a.pull = c->pulled;
+            C rs[4];
+            ref_sums(c, rs);
+            a.rsf_hi = rs[0];
+            a.rsf_lo = rs[1];
+            a.rsg_hi = rs[2];
+            a.rsg_lo = rs[3];
+            a.fi = (const T *)c->f[c->cur];
+            a.fo = (T *)c->f[1 - c->cur];
+            hipLaunchKernelGGL((k_block2d<S, WALL, NT>), dim3((unsigned)((c->p.nx + a.own - 1) / a.own)),
+                               dim3((unsigned)((c->b2_threads + 63) / 64 * 64)), 0, c->stream, a);
+        }
+    }
+    // at most b2_steps steps
+    static void block2d_launch(lbm_ctx *c, int steps) {
+        constexpr int BIG = std::is_same<C, double>::value ? 512 : 1024;
+        const bool small = c->b2_threads <= 256;
+        if (c->grid.wallx) small ? block2d_run<true, 256>(c, steps) : block2d_run<true, 512>(c, steps);
+        else small ? block2d_run<false, 256>(c, steps) : block2d_run<false, BIG>(c, steps);
+        c->cur = 1 - c->cur;
+        c->pulled = c->grid.wallx ? 0 : 1;
+    }
+    static int block2d_step(lbm_ctx *c, int n) {
+        const long long every = c->p.check_every;
+        while (n > 0) {
+            int k = std::min(n, c->b2_steps);
+            if (every > 0) k = (int)std::min<long long>(k, every - c->steps_done % every);
+            block2d_launch(c, k);
+            int rc = last_launch();
+            if (rc) return rc;
+            n -= k;
+            c->steps_done += k;
+            if (every > 0 && c->steps_done % every == 0) {
+                double tmp[RED_VALS];
+                rc = conservation(c, tmp);
+                if (rc) return rc;
+            }
+        }
+        return LBM_OK;
+    }
     static int step(lbm_ctx *c, int n) {
+        if (c->b2_threads) return block2d_step(c, n);
         Fields<C> fl = get_fields<C>(c);
         for (int s = 0; s < n; s++) {
             int rc;
@@ -570,6 +662,22 @@ template <int D, class S> struct Impl {
         hipEvent_t ev[5];
         for (int k = 0; k < 5; k++)
             if (hipEventCreate(&ev[k]) != hipSuccess) return LBM_EDEVICE;
+        if (c->b2_threads) {  // one kind, its time per step
+            (void)hipEventRecord(ev[0], c->stream);
+            int rc = LBM_OK;
+            for (int left = n; left > 0 && rc == LBM_OK; left -= c->b2_steps) {
+                block2d_launch(c, std::min(left, c->b2_steps));
+                rc = last_launch();
+            }
+            (void)hipEventRecord(ev[1], c->stream);
+            float ms = 0;
+            if (rc == LBM_OK && (hipEventSynchronize(ev[1]) != hipSuccess ||
+                                 hipEventElapsedTime(&ms, ev[0], ev[1]) != hipSuccess))
+                rc = LBM_EDEVICE;
+            for (int k = 0; k < 5; k++) (void)hipEventDestroy(ev[k]);
+            for (int k = 0; k < LBM_NUM_KERNELS; k++) host_ms[k] = k == 0 && n > 0 ? (double)ms / n : 0.0;
+            return rc;
+        }
         if (c->fused) {
             // kinds: 0 k_fused, 1 k_fused_fixup, 2 k_eos_surrogate
             double acc[3] = {0, 0, 0};
@@ -849,6 +957,8 @@ int lbm_create(const lbm_params *params, lbm_ctx **out) {
             c->fused = false;
     }
     if (!c->fused) c->folded = false;
+    auto plan2d = [&]() { DISPATCH_VOID(c, block2d_plan(c)); };
+    plan2d();
     // field arrays: rho, J[D], G, lap (all that a read-back of the fused path
     // uses); the multi-kernel path's also u[D], F[D], Lam[D], T, P, h, cs2, with
     // Peng-Robinson e(rho, T), and the four shock-capturing work arrays when
@@ -992,6 +1102,7 @@ const char *lbm_last_error(void) { return g_last_error; }
 
 const char *lbm_kernel_name(const lbm_ctx *c, int k) {
     static const char *names[LBM_NUM_KERNELS] = {"k_moments", "k_lap", "k_fields", "k_collide"};
+    if (c && c->b2_threads) return k == 0 ? "k_block2d" : "";
     if (c && c->fused)  // folded: the surrogate pass does the fix-up's work but on the segment-end planes
         return k == 0 ? "k_fused"
                       : (k == 1 ? (c->folded && c->p.lattice == 2 ? "" : "k_fused_fixup")

@@ -46,6 +46,8 @@ struct lbm_ctx {
     int mcc = 0;
     bool mc_pending = false;
     bool folded = false;  // the surrogate pass completes the side channel (the fix-up only its segment-end planes)
+    // small D2Q9 lattices: several steps in one launch (0 threads: not)
+    int b2_threads = 0, b2_own = 0, b2_halo = 0, b2_steps = 0;
     size_t mc_bytes = 0, in_bytes = 0;
     int ntx = 0, nty = 0, nseg = 1, nlay = 0, chunk = 0;
 };

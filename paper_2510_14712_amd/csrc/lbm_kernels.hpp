@@ -473,7 +473,7 @@ __global__ void __launch_bounds__(BX) k_sc_filter(Grid g, int axis, ScFilter<C> 
 // the ghost buffer gb[side][(z ny + y) Q + i]; k_wall_emit then writes what
 // each ghost emits.
 template <class C> struct WallGhost {
-    C u[3], T, theta, e, h;
+    C u[3], T, theta, e, h, Lx;  // Lx: Lambda_x
 };
 template <class C> __device__ __forceinline__ WallGhost<C> wall_ghost(const Phys<C> &ph, const Walls &w, int side,
                                                                       C rho_b) {
@@ -492,6 +492,7 @@ template <class C> __device__ __forceinline__ WallGhost<C> wall_ghost(const Phys
     gs.theta = P / rho_b;
     gs.e = e;
     gs.h = e + gs.theta;
+    gs.Lx = rho_b * gs.u[0] * gs.u[0] * gs.u[0] + C(3) * rho_b * gs.u[0] * (gs.theta - C(1.0 / 3.0));
     return gs;
 }
 
@@ -595,7 +596,7 @@ __global__ void __launch_bounds__(BX) k_collide(Grid g, Phys<typename S::C> ph, 
                 nu[k] = gs.u[0];
                 nh[k] = gs.h;
                 nT[k] = gs.T;
-                nL[k] = rho * gs.u[0] * gs.u[0] * gs.u[0] + C(3) * rho * gs.u[0] * (gs.theta - C(1.0 / 3.0));
+                nL[k] = gs.Lx;
             }
         }
         divu += C(0.5) * (nu[1] - nu[0]);

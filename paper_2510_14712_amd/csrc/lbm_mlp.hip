@@ -5,10 +5,11 @@
 // with a residual check and an exact FP64 Newton fallback; training uses the
 // library's own forward, backward and Adam kernels.
 //
-// In training one wavefront handles 64 samples.  The 64x64 hidden layer and the
-// two 64x64x64 products of the backward pass run through wave_gemm64: BF16
-// MFMA (v_mfma_f32_32x32x16_bf16, FP32 accumulate) or FP32 on the vector ALU,
-// both returning the result in the MFMA accumulator layout:
+// In training a workgroup of four wavefronts handles 64 samples.  The 64x64
+// hidden layer and the two 64x64x64 products of the backward pass run through
+// wave_tile64, a 32x32 tile per wavefront: BF16 MFMA (v_mfma_f32_32x32x16_bf16,
+// FP32 accumulate) or FP32 MFMA (v_mfma_f32_32x32x2_f32), both returning the
+// result in the accumulator layout:
 //   tile (mt, nt) in {0,1}^2, accumulator v in 0..15, lane l holds
 //   row 32 mt + 8 (v / 4) + 4 (l / 32) + v % 4, column 32 nt + l % 32.
 #include <hip/hip_runtime.h>
@@ -34,43 +35,36 @@ constexpr int LD = 65;  // padded LDS row stride (floats) of a 64x64 activation 
 __device__ __forceinline__ int acc_row(int mt, int v, int lane) { return 32 * mt + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 __device__ __forceinline__ int acc_col(int nt, int lane) { return 32 * nt + (lane & 31); }
 
-// C(i, j) = sum_k A(i, k) B(k, j), i, j, k in [0, 64); A and B are strided
-// FP32 views: A(i, k) = A[i * ai + k * ak], B(k, j) = B[k * bk + j * bj].
-// acc[(mt * 2 + nt) * 16 + v] receives the entry at (acc_row, acc_col).
-template <bool MFMA>
-__device__ __forceinline__ void wave_gemm64(const float *A, int ai, int ak, const float *B, int bk, int bj,
-                                            float acc[64]) {
-    const int lane = threadIdx.x & 63;
-    if constexpr (MFMA) {
-        f32x16 c[4];
-        for (int t = 0; t < 4; t++)
-            for (int v = 0; v < 16; v++) c[t][v] = 0.0f;
+// Tile (mt, nt) of C(i, j) = sum_k A(i, k) B(k, j), i, j, k in [0, 64), by one
+// wavefront; A and B are strided FP32 views: A(i, k) = A[i * ai + k * ak],
+// B(k, j) = B[k * bk + j * bj].  Entry v of the result is the one at (acc_row,
+// acc_col).  BF16: operands rounded to BF16; else the FP32 matrix instruction.
+template <bool BF16>
+__device__ __forceinline__ f32x16 wave_tile64(const float *A, int ai, int ak, const float *B, int bk, int bj, int mt,
+                                              int nt) {
+    const int lane = threadIdx.x & 63, i = 32 * mt + (lane & 31), j = 32 * nt + (lane & 31);
+    f32x16 c;
+    for (int v = 0; v < 16; v++) c[v] = 0.0f;
+    if constexpr (BF16) {
+#pragma unroll
         for (int ks = 0; ks < 4; ks++) {
-            bf16x8 a[2], b[2];
+            bf16x8 a, b;
             const int k0 = 16 * ks + 8 * (lane >> 5);
-            for (int m = 0; m < 2; m++) {
-                const int i = 32 * m + (lane & 31);
-                for (int j = 0; j < 8; j++) {
-                    a[m][j] = to_bf16(A[i * ai + (k0 + j) * ak]);
-                    b[m][j] = to_bf16(B[(k0 + j) * bk + i * bj]);
-                }
+#pragma unroll
+            for (int q = 0; q < 8; q++) {
+                a[q] = to_bf16(A[i * ai + (k0 + q) * ak]);
+                b[q] = to_bf16(B[(k0 + q) * bk + j * bj]);
             }
-            for (int mt = 0; mt < 2; mt++)
-                for (int nt = 0; nt < 2; nt++)
-                    c[mt * 2 + nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt], b[nt], c[mt * 2 + nt], 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
         }
-        for (int t = 0; t < 4; t++)
-            for (int v = 0; v < 16; v++) acc[t * 16 + v] = c[t][v];
     } else {
-        for (int mt = 0; mt < 2; mt++)
-            for (int nt = 0; nt < 2; nt++)
-                for (int v = 0; v < 16; v++) {
-                    const int i = acc_row(mt, v, lane), j = acc_col(nt, lane);
-                    float s = 0.0f;
-                    for (int k = 0; k < 64; k++) s = fmaf(A[i * ai + k * ak], B[k * bk + j * bj], s);
-                    acc[(mt * 2 + nt) * 16 + v] = s;
-                }
+#pragma unroll 8
+        for (int s = 0; s < 32; s++) {
+            const int k = 2 * s + (lane >> 5);
+            c = __builtin_amdgcn_mfma_f32_32x32x2f32(A[i * ai + k * ak], B[k * bk + j * bj], c, 0, 0, 0);
+        }
     }
+    return c;
 }
 
 // ---------------------------------------------------------------------------
@@ -234,118 +228,165 @@ __global__ void __launch_bounds__(BX, 2) k_cells_mlp(Grid g, Phys<float> ph, Mom
 }
 
 // ---------------------------------------------------------------------------
-// Training.  One wave per block processes 64 samples of the batch and writes
-// its partial gradient (NP values) and partial squared error; a second kernel
-// sums the partials in block order.  Loss L = 1/(3B) sum (yhat - that)^2.
-template <bool MFMA>
-__global__ void __launch_bounds__(64) k_train_partial(const float *__restrict__ P, const float *__restrict__ xn,
-                                                     const float *__restrict__ tn, int B, float *__restrict__ gpart,
-                                                     float *__restrict__ lpart) {
-    __shared__ float H1[64 * LD], H2[64 * LD], DZ[64 * LD], X[64 * 2], DY[64 * 3];
-    const int lane = threadIdx.x;
+// Training.  A workgroup processes 64 samples of the batch and writes its
+// partial gradient (NP values) and partial squared error; a second kernel sums
+// the partials in a fixed order.  Loss L = 1/(3B) sum (yhat - that)^2.
+//
+// Bound by latency: a chain of LDS passes with a barrier between them, each sum
+// over samples or neurons in sequence by one lane.  The four wavefronts share
+// every pass -- a tile of each product, a quarter of the rows, or one of the
+// independent sums each (8192 samples, BF16: 17.6 us with one wavefront doing
+// all of them, now 9.6, of which the loads and the launch are about half).
+template <bool BF16>
+__global__ void __launch_bounds__(256) k_train_partial(const float *__restrict__ P, const float *__restrict__ xn,
+                                                       const float *__restrict__ tn, int B, float *__restrict__ gpart,
+                                                       float *__restrict__ lpart) {
+    __shared__ float H1[64 * LD], H2[64 * LD], DZ[64 * LD], W2[64 * LD], X[64 * 2], DY[64 * 3];
+    __shared__ float Pr[3 * 64];  // squared residuals
+    __shared__ float sB2[H], sW3[3 * H + 3];  // b2; w3, b3
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int mt = w >> 1, nt = w & 1;  // this wavefront's tile of each product
     const int b = blockIdx.x * 64 + lane;
     float *G = gpart + (long long)blockIdx.x * NP;
-    const float x0 = xn[2 * b], x1 = xn[2 * b + 1];
-    X[2 * lane] = x0;
-    X[2 * lane + 1] = x1;
-    for (int j = 0; j < H; j++)
+    // every load of the kernel first: behind a barrier each would cost its
+    // latency again (the parameters are the last update's, fresh from memory)
+    const float x0 = xn[2 * b], x1 = xn[2 * b + 1], target = w < 3 ? tn[3 * b + w] : 0.0f;
+    if (threadIdx.x < H) sB2[threadIdx.x] = P[OFF_B2 + threadIdx.x];
+    if (threadIdx.x < 3 * H + 3) sW3[threadIdx.x] = P[OFF_W3 + threadIdx.x];
+    if (w == 0) {
+        X[2 * lane] = x0;
+        X[2 * lane + 1] = x1;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        const int q = threadIdx.x + 256 * r;
+        W2[(q / H) * LD + q % H] = P[OFF_W2 + q];
+    }
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        const int j = 16 * w + r;
         H1[lane * LD + j] = relu(fmaf(P[OFF_W1 + 2 * j], x0, fmaf(P[OFF_W1 + 2 * j + 1], x1, P[OFF_B1 + j])));
+    }
     __syncthreads();
-    float acc[64];
-    wave_gemm64<MFMA>(H1, LD, 1, P + OFF_W2, 1, H, acc);   // Z2 = H1 W2^T
-    for (int t = 0; t < 4; t++)
-        for (int v = 0; v < 16; v++) {
-            const int r = acc_row(t >> 1, v, lane), cc = acc_col(t & 1, lane);
-            H2[r * LD + cc] = relu(acc[t * 16 + v] + P[OFF_B2 + cc]);
-        }
+    {
+        const f32x16 acc = wave_tile64<BF16>(H1, LD, 1, W2, 1, LD, mt, nt);  // Z2 = H1 W2^T
+        const int cc = acc_col(nt, lane);
+        const float b2 = sB2[cc];
+#pragma unroll
+        for (int v = 0; v < 16; v++) H2[acc_row(mt, v, lane) * LD + cc] = relu(acc[v] + b2);
+    }
     __syncthreads();
+    // output k = w of the lane's sample, and its residual
     const float scale = 2.0f / (3.0f * (float)B);
-    float sq = 0.0f;
-    for (int k = 0; k < 3; k++) {
-        float s = P[OFF_B3 + k];
-        for (int n = 0; n < H; n++) s = fmaf(P[OFF_W3 + k * H + n], H2[lane * LD + n], s);
-        float r = s - tn[3 * b + k];
-        sq += r * r;
-        DY[3 * lane + k] = scale * r;   // dL / dyhat
-    }
-    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
-    if (lane == 0) lpart[blockIdx.x] = sq;
-    __syncthreads();
-    // output layer: dW3[k][n] = sum_b DY[b][k] H2[b][n]; db3[k] = sum_b DY[b][k]
-    for (int k = 0; k < 3; k++) {
-        float s = 0.0f;
-        for (int bb = 0; bb < 64; bb++) s = fmaf(DY[3 * bb + k], H2[bb * LD + lane], s);
-        G[OFF_W3 + k * H + lane] = s;
-    }
-    if (lane < 3) {
-        float s = 0.0f;
-        for (int bb = 0; bb < 64; bb++) s += DY[3 * bb + lane];
-        G[OFF_B3 + lane] = s;
-    }
-    // dZ2[b][n] = (sum_k DY[b][k] W3[k][n]) ReLU'(z2), lane n over all b (the
-    // unit is active where its output H2 is positive)
-    for (int bb = 0; bb < 64; bb++) {
-        float h2 = H2[bb * LD + lane];
-        float d = DY[3 * bb] * P[OFF_W3 + lane] + DY[3 * bb + 1] * P[OFF_W3 + H + lane] +
-                  DY[3 * bb + 2] * P[OFF_W3 + 2 * H + lane];
-        DZ[bb * LD + lane] = h2 > 0.0f ? d : 0.0f;  // ReLU'
+    if (w < 3) {
+        float s = sW3[3 * H + w];
+#pragma unroll 16
+        for (int n = 0; n < H; n++) s = fmaf(sW3[w * H + n], H2[lane * LD + n], s);
+        const float r = s - target;
+        Pr[64 * w + lane] = r * r;
+        DY[3 * lane + w] = scale * r;  // dL / dyhat
     }
     __syncthreads();
-    {   // db2[n] = sum_b dZ2[b][n]
-        float s = 0.0f;
-        for (int bb = 0; bb < 64; bb++) s += DZ[bb * LD + lane];
-        G[OFF_B2 + lane] = s;
+    // dZ2[b][n] = (sum_k DY[b][k] W3[k][n]) ReLU'(z2), lane n, a quarter of the
+    // samples (the unit is active where its output H2 is positive)
+    {
+        const float w0 = sW3[lane], w1 = sW3[H + lane], w2 = sW3[2 * H + lane];
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            const int bb = 16 * w + r;
+            float h2 = H2[bb * LD + lane];
+            float d = DY[3 * bb] * w0 + DY[3 * bb + 1] * w1 + DY[3 * bb + 2] * w2;
+            DZ[bb * LD + lane] = h2 > 0.0f ? d : 0.0f;  // ReLU'
+        }
     }
+    // output layer: dW3[k][n] = sum_b DY[b][k] H2[b][n], k = w; db3[k] = sum_b
+    // DY[b][k] and the loss by the fourth wavefront
+    if (w < 3) {
+        float s = 0.0f;
+#pragma unroll 16
+        for (int bb = 0; bb < 64; bb++) s = fmaf(DY[3 * bb + w], H2[bb * LD + lane], s);
+        G[OFF_W3 + w * H + lane] = s;
+    } else {
+        if (lane < 3) {
+            float s = 0.0f;
+#pragma unroll 16
+            for (int bb = 0; bb < 64; bb++) s += DY[3 * bb + lane];
+            G[OFF_B3 + lane] = s;
+        }
+        float sq = (Pr[lane] + Pr[64 + lane]) + Pr[128 + lane];
+        for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+        if (lane == 0) lpart[blockIdx.x] = sq;
+    }
+    __syncthreads();
     // dW2[n][k] = sum_b dZ2[b][n] H1[b][k]
-    wave_gemm64<MFMA>(DZ, 1, LD, H1, LD, 1, acc);
-    for (int t = 0; t < 4; t++)
-        for (int v = 0; v < 16; v++)
-            G[OFF_W2 + acc_row(t >> 1, v, lane) * H + acc_col(t & 1, lane)] = acc[t * 16 + v];
-    // dH1[b][k] = sum_n dZ2[b][n] W2[n][k]
-    wave_gemm64<MFMA>(DZ, LD, 1, P + OFF_W2, H, 1, acc);
-    __syncthreads();
-    for (int t = 0; t < 4; t++)
+    {
+        const f32x16 acc = wave_tile64<BF16>(DZ, 1, LD, H1, LD, 1, mt, nt);
+#pragma unroll
+        for (int v = 0; v < 16; v++) G[OFF_W2 + acc_row(mt, v, lane) * H + acc_col(nt, lane)] = acc[v];
+    }
+    // dH1[b][k] = sum_n dZ2[b][n] W2[n][k], then dZ1 in the place of H2
+    {
+        const f32x16 acc = wave_tile64<BF16>(DZ, LD, 1, W2, LD, 1, mt, nt);
+        const int cc = acc_col(nt, lane);
+#pragma unroll
         for (int v = 0; v < 16; v++) {
-            const int r = acc_row(t >> 1, v, lane), cc = acc_col(t & 1, lane);
-            float h1 = H1[r * LD + cc];
-            H2[r * LD + cc] = h1 > 0.0f ? acc[t * 16 + v] : 0.0f;  // dZ1, reusing H2
+            const int r = acc_row(mt, v, lane);
+            H2[r * LD + cc] = H1[r * LD + cc] > 0.0f ? acc[v] : 0.0f;
         }
+    }
     __syncthreads();
-    {   // dW1[j][i] = sum_b dZ1[b][j] X[b][i]; db1[j] = sum_b dZ1[b][j]
-        float s0 = 0.0f, s1 = 0.0f, sb = 0.0f;
-        for (int bb = 0; bb < 64; bb++) {
-            float d = H2[bb * LD + lane];
-            s0 = fmaf(d, X[2 * bb], s0);
-            s1 = fmaf(d, X[2 * bb + 1], s1);
-            sb += d;
+    // lane n, j: db2[n] = sum_b dZ2[b][n]; dW1[j][i] = sum_b dZ1[b][j] X[b][i];
+    // db1[j] = sum_b dZ1[b][j]; one of the four sums per wavefront
+    {
+        const float *D = w == 3 ? DZ : H2;
+        float s = 0.0f;
+        if (w < 2) {
+#pragma unroll 16
+            for (int bb = 0; bb < 64; bb++) s = fmaf(D[bb * LD + lane], X[2 * bb + w], s);
+            G[OFF_W1 + 2 * lane + w] = s;
+        } else {
+#pragma unroll 16
+            for (int bb = 0; bb < 64; bb++) s += D[bb * LD + lane];
+            G[(w == 2 ? OFF_B1 : OFF_B2) + lane] = s;
         }
-        G[OFF_W1 + 2 * lane] = s0;
-        G[OFF_W1 + 2 * lane + 1] = s1;
-        G[OFF_B1 + lane] = sb;
     }
 }
 
-// Sum of the per-block partial gradients, in a fixed order: a workgroup
-// takes 64 parameters; its four wavefronts each sum a contiguous quarter of
-// the blocks for those parameters (a lane per parameter, loads coalesced
-// across the lanes), and lane p of the first wavefront adds the four quarter
-// sums in order.  The loss: FP64 sum of the block losses by one lane.
-__global__ void __launch_bounds__(256) k_sum_partials(const float *gpart, const float *lpart, int nblk, int B,
-                                                      float *grad, float *loss) {
-    __shared__ float part[4][64];
+// Sum of the per-block partial gradients, in a fixed order: a workgroup takes
+// 64 parameters; its 16 wavefronts each sum a contiguous sixteenth of the blocks
+// for those parameters (a lane per parameter, loads coalesced across the lanes
+// and eight in flight), and lane p of the first wavefront adds the sums in order.
+// The last workgroup sums the block losses in FP64.  Bound by the latency of the
+// partials, which other XCDs have written (128 blocks: 17.6 us with four
+// wavefronts and one lane adding up the losses, now 3.9).
+constexpr int SUM_WAVES = 16;
+__global__ void __launch_bounds__(64 * SUM_WAVES) k_sum_partials(const float *__restrict__ gpart,
+                                                                 const float *__restrict__ lpart, int nblk, int B,
+                                                                 float *__restrict__ grad, float *__restrict__ loss) {
+    __shared__ float part[SUM_WAVES][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (blockIdx.x == gridDim.x - 1) {
+        if (w || !loss) return;
+        double t = 0.0;
+        for (int k = lane; k < nblk; k += 64) t += (double)lpart[k];
+        t = wave_sum(t);
+        if (lane == 0) loss[0] = (float)(t / (3.0 * (double)B));
+        return;
+    }
     const int p = blockIdx.x * 64 + lane;
-    const int k0 = (int)(((long long)w * nblk) / 4), k1 = (int)(((long long)(w + 1) * nblk) / 4);
+    const int k0 = (int)(((long long)w * nblk) / SUM_WAVES), k1 = (int)(((long long)(w + 1) * nblk) / SUM_WAVES);
     float s = 0.0f;
-    if (p < NP)
+    if (p < NP) {
+#pragma unroll 8
         for (int k = k0; k < k1; k++) s += gpart[(long long)k * NP + p];
+    }
     part[w][lane] = s;
     __syncthreads();
-    if (w == 0 && p < NP) grad[p] = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
-    if (blockIdx.x == 0 && threadIdx.x == 0 && loss) {
-        double t = 0.0;
-        for (int k = 0; k < nblk; k++) t += (double)lpart[k];
-        loss[0] = (float)(t / (3.0 * (double)B));
+    if (w == 0 && p < NP) {
+        float t = part[0][lane];
+#pragma unroll
+        for (int q = 1; q < SUM_WAVES; q++) t += part[q][lane];
+        grad[p] = t;
     }
 }
 
@@ -579,11 +620,11 @@ static int loss_grad_impl(const float *params, const float *xn, const float *tn,
                           int precision, hipStream_t s, float *gpart, float *lpart) {
     const int nblk = B / 64;
     if (precision == LBM_MLP_BF16)
-        hipLaunchKernelGGL(mlp::k_train_partial<true>, dim3(nblk), dim3(64), 0, s, params, xn, tn, B, gpart, lpart);
+        hipLaunchKernelGGL(mlp::k_train_partial<true>, dim3(nblk), dim3(256), 0, s, params, xn, tn, B, gpart, lpart);
     else
-        hipLaunchKernelGGL(mlp::k_train_partial<false>, dim3(nblk), dim3(64), 0, s, params, xn, tn, B, gpart, lpart);
-    hipLaunchKernelGGL(mlp::k_sum_partials, dim3((mlp::NP + 63) / 64), dim3(256), 0, s, gpart, lpart, nblk, B,
-                       grad, loss);
+        hipLaunchKernelGGL(mlp::k_train_partial<false>, dim3(nblk), dim3(256), 0, s, params, xn, tn, B, gpart, lpart);
+    hipLaunchKernelGGL(mlp::k_sum_partials, dim3((mlp::NP + 63) / 64 + 1), dim3(64 * mlp::SUM_WAVES), 0, s, gpart,
+                       lpart, nblk, B, grad, loss);
     return lbm_note(hipGetLastError());
 }
 

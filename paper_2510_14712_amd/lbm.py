@@ -111,22 +111,36 @@ def _check(status, what):
         raise LbmError(status, what)
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _stream_ptr(stream=None):
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """The raw stream handle: of `stream`, or of torch's current one (asked for
+    as a handle where torch offers that: 0.1 us, a Stream object takes 2.9)."""
+    if stream is not None:
+        return stream.cuda_stream
+    cuda = _torch().cuda
+    raw = getattr(_torch()._C, "_cuda_getCurrentRawStream", None)
+    return raw(cuda.current_device()) if raw is not None else cuda.current_stream().cuda_stream
 
 
 def _dev(arr, dtype, n=None):
     """Contiguous CUDA tensor of the given torch dtype (copies host arrays)."""
     torch = _torch()
     if isinstance(arr, torch.Tensor):
-        t = arr.to(device="cuda", dtype=dtype).contiguous()
+        # a tensor that needs nothing passes as it is (.to and .contiguous would
+        # return it too, at 2 us a tensor: a training step hands over seven)
+        t = arr
+        if not (t.is_cuda and t.dtype is dtype and t.is_contiguous()) or t.device.index != torch.cuda.current_device():
+            t = arr.to(device="cuda", dtype=dtype).contiguous()
     else:
         t = torch.as_tensor(np.ascontiguousarray(arr)).to(device="cuda", dtype=dtype).contiguous()
     if n is not None and t.numel() != n:
@@ -135,7 +149,7 @@ def _dev(arr, dtype, n=None):
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else 0
 
 
 class Lattice:
@@ -176,7 +190,7 @@ class Lattice:
         if pr is not None:  # Peng-Robinson constants dict(m, Tc, c0, c1); a, b, R above
             p.pr_m, p.pr_Tc, p.pr_c0, p.pr_c1 = (float(pr[k]) for k in ("m", "Tc", "c0", "c1"))
         self._stream = stream
-        p.stream = _stream_ptr(stream).value if _torch().cuda.is_available() else None
+        p.stream = _stream_ptr(stream) if _torch().cuda.is_available() else None
         self.params = p
         h = _VP()
         _check(L.lbm_create(ctypes.byref(p), ctypes.byref(h)), "lbm_create")
@@ -347,8 +361,9 @@ def mlp_loss_grad_noalloc(params, xn, tn, precision=MLP_BF16, stream=None, out=N
 
 def mlp_adam(params, grad, m, v, t, lr, stream=None):
     """lbm_mlp_adam on CUDA float32 tensors of 4547 values (updated in place)."""
+    f32 = _torch().float32
     for a in (params, grad, m, v):
-        assert a.is_cuda and a.dtype == _torch().float32 and a.is_contiguous() and a.numel() == MLP_NPARAMS
+        assert a.is_cuda and a.dtype == f32 and a.is_contiguous() and a.numel() == MLP_NPARAMS
     _check(load().lbm_mlp_adam(_ptr(params), _ptr(grad), _ptr(m), _ptr(v), int(t), float(lr), _stream_ptr(stream)),
            "lbm_mlp_adam")
 

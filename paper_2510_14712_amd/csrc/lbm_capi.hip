@@ -209,12 +209,13 @@ static void make_ref(const lbm_params &p, int D, RefPops &ref) {
 // ---------------------------------------------------------------------------
 // dispatch over (lattice, storage)
 // ---------------------------------------------------------------------------
-// tile of the fused step.  FP64 uses a smaller tile to fit the LDS budget;
-// the other forms take a wide 64 x 4 tile (fewer x-shifted row fragments per
-// plane; measured faster than 32 x 8 for FP32 and, fix-up pass included,
-// for BF16).
+// tile of the fused step.  The FP32 and 16-bit forms take a wide 64 x 4 tile
+// (fewer x-shifted row fragments per plane; measured faster than 32 x 8 for
+// FP32 and, fix-up pass included, for BF16).  FP64, bound by arithmetic and by
+// latency, takes 32 x 8: the fewest ring cells per cell of 256 (a 16 x 8 tile
+// left two of a compute unit's four SIMDs idle).
 template <class S, bool MLP>
-using TileOf = typename std::conditional<std::is_same<S, StoreF64>::value, Tile<16, 8>, Tile<64, 4>>::type;
+using TileOf = typename std::conditional<std::is_same<S, StoreF64>::value, Tile<32, 8>, Tile<64, 4>>::type;
 
 template <int D, class S> struct Impl {
     using C = typename S::C;
@@ -283,6 +284,7 @@ template <int D, class S> struct Impl {
         a.ntx = c->ntx;
         a.nty = c->nty;
         a.nseg = c->nseg;
+        a.nsub = c->nsub;
         a.nlay = c->nlay;
         a.chunk = c->chunk;
         a.pull = c->pulled;
@@ -305,7 +307,7 @@ template <int D, class S> struct Impl {
         a.Acc = (const unsigned *)c->Acc;
         a.accw = 2 * ((c->p.nx + 63) / 64);
         a.inv_cv_d = 1.0 / (double)(float)c->p.cv;
-        const dim3 grid((unsigned)(c->ntx * c->nty * c->nseg));
+        const dim3 grid((unsigned)(c->ntx * c->nty * c->nseg * c->nsub));
         const bool fast = fast_instance<M>(c);
         if constexpr (M && std::is_same<C, float>::value) {
             if (fast) hipLaunchKernelGGL((k_fused<D, S, TL, true, true>), grid, dim3(TL::NT), 0, c->stream, a);
@@ -753,6 +755,38 @@ template <int D, class S> struct Impl {
         mlp(c) ? tiles_t<true>(c) : tiles_t<false>(c);
         c->folded = fold(c);
     }
+    // Resident workgroups of the fused step: compute units x the kernel's
+    // occupancy (the instance the step launches); 0 if the device cannot be
+    // queried
+    template <bool M> static long long resident_groups() {
+        using TL = TileOf<S, M>;
+        int dev = 0, ncu = 0, nb = 0;
+        const bool known =
+            hipGetDevice(&dev) == hipSuccess &&
+            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &nb, k_fused<D, S, TL, M && std::is_same<C, float>::value, false>, TL::NT, 0) == hipSuccess &&
+            ncu > 0 && nb > 0;
+        if (!known) (void)hipGetLastError();
+        return known ? (long long)ncu * nb : 0;
+    }
+    // Workgroups per tile and segment.  A march takes about its planes plus four
+    // (the prologue), and two planes more where several share a segment; more of
+    // them pay where the tiles and segments leave compute units without work
+    // (us per step, FP32, 1 against the number taken: 11 x 11 x 28 cells 204
+    // against 47, 100 x 75 x 60 166 against 112).
+    static int sub_marches(const lbm_ctx *c, long long ntiles, long long res) {
+        if (!res) return 1;
+        const int planes = (c->p.nz + c->nseg - 1) / c->nseg;
+        auto cost = [&](int m) {
+            const long long rounds = (ntiles * c->nseg * m + res - 1) / res;
+            return rounds * ((planes + m - 1) / m + (m > 1 ? 2 : 0) + 4);
+        };
+        int best = 1;
+        for (int m = 2; m <= planes; m++)
+            if (cost(m) < cost(best)) best = m;
+        return cost(best) * 20 <= cost(1) * 19 ? best : 1;
+    }
     template <bool M> static void tiles_t(lbm_ctx *c) {
         using TL = TileOf<S, M>;
         c->ntx = (c->p.nx + TL::TX - 1) / TL::TX;
@@ -772,23 +806,24 @@ template <int D, class S> struct Impl {
             // two rounds ends on its slowest workgroups (512^3, 16-bit: one
             // segment, two rounds, 9.6 ms; four segments 9.0 ms); without
             // such segments the first count reaching 1024 workgroups.
-            // Resident workgroups: compute units x the fused kernel's
-            // occupancy (the instance the step launches); if the device
-            // cannot be queried, the first count giving 1024 workgroups.
+            // If the device cannot be queried, the first count giving 1024
+            // workgroups.
             const int smax = std::max(1, c->p.nz / 16);
-            int dev = 0, ncu = 0, nb = 0;
-            const bool known =
-                hipGetDevice(&dev) == hipSuccess &&
-                hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-                hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                    &nb, k_fused<D, S, TL, M && std::is_same<C, float>::value, false>, TL::NT, 0) ==
-                    hipSuccess &&
-                ncu > 0 && nb > 0;
-            if (!known) {
-                (void)hipGetLastError();
+            const long long res = resident_groups<M>();
+            if (std::is_same<C, double>::value && res && ntiles * smax < res) {
+                // FP64 where such segments leave compute units without work:
+                // the shortest march with its prologue of about four planes
+                // (100 x 75 x 60 cells: 6 segments 146 us per step, 3 shared by
+                // two workgroups each 159).  The other forms keep the count,
+                // which the last bits of their sums depend on.
+                const int nz = c->p.nz;
+                auto march = [&](int s) { return ((ntiles * s + res - 1) / res) * ((nz + s - 1) / s + 4); };
+                c->nseg = 1;
+                for (int s = 2; s <= std::max(1, nz / 4); s++)
+                    if (march(s) < march(c->nseg)) c->nseg = s;
+            } else if (!res) {
                 c->nseg = std::max(1, std::min((int)((1024 + ntiles - 1) / ntiles), smax));
             } else {
-                const long long res = (long long)ncu * nb;
                 const int nz = c->p.nz;
                 auto cost = [&](int s) { return ((ntiles * s + res - 1) / res) * ((nz + s - 1) / s); };
                 long long best_cost = -1;
@@ -810,7 +845,8 @@ template <int D, class S> struct Impl {
             }
         }
         c->nlay = D == 3 ? c->p.nz + 2 * c->nseg : 1;
-        const long long total = ntiles * c->nseg;
+        c->nsub = D == 3 ? sub_marches(c, ntiles, resident_groups<M>()) : 1;
+        const long long total = ntiles * c->nseg * c->nsub;
         c->chunk = total % 8 == 0 ? (int)(total / 8) : 0;
         c->mc_bytes = sizeof(C) * 5 * (size_t)c->nlay * c->p.nx * c->p.ny;
         c->in_bytes = sizeof(C) * (size_t)ntiles * c->nlay * 5 * TL::NR;

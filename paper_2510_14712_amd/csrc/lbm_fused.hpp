@@ -76,6 +76,7 @@ template <class C, class T> struct FusedArgs {
     Phys<C> ph;
     RefPops ref;
     int ntx, nty, nseg;  // tiles along x, y; z segments
+    int nsub;            // workgroups that share a tile's march through a segment
     int nlay;            // layers of Mc / IN: nz planes + 2 spill layers per segment (D = 3), 1 (D = 2)
     int chunk;           // tiles per XCD in the remapped order, 0: identity order
     int pull;            // form of the input set: 0 arrived, 1 post-collision (read from x - c_i)
@@ -761,8 +762,12 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
     __shared__ C sLap[NLS][TL::R2];
     __shared__ C sRing[NFS][NRF][TL::R1];
     using XT = typename S::X;
-    constexpr int GROW = Q;          // first exchange row of g
-    __shared__ XT sX[2 * Q][XS];  // exchange: deviations of the collided f (rows 0..Q-1) and g
+    // FP64 on D3Q27 exchanges f and g in turn: both at once would not fit the
+    // LDS beside the other arrays with a wavefront on every SIMD
+    constexpr bool TURN = D == 3 && sizeof(XT) == 8;
+    constexpr int GROW = TURN ? 0 : Q;   // first exchange row of g
+    constexpr int NX = TURN ? Q : 2 * Q;  // exchange rows
+    __shared__ XT sX[NX][XS];  // exchange: deviations of the collided f (rows 0..Q-1) and g
     __shared__ C sRacc[D == 3 ? 3 : 1][5][TL::NR];  // moment sums of the ring destinations, by plane
 
     Grid g = a.g;
@@ -789,12 +794,22 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
     // -- tile and segment of this workgroup ----------------------------------
     const int b = blockIdx.x;
     const int L = a.chunk ? (b & 7) * a.chunk + (b >> 3) : b;
-    const int tx = L % a.ntx, ty = (L / a.ntx) % a.nty, seg = L / (a.ntx * a.nty);
+    const int tx = L % a.ntx, ty = (L / a.ntx) % a.nty, part = L / (a.ntx * a.nty);
+    const int seg = part / a.nsub, nth = part - seg * a.nsub;
     const int x0 = tx * TX, y0 = ty * TY;
     const int w = FAST ? TX : min(TX, g.nx - x0), h = FAST ? TY : min(TY, g.ny - y0);
     const int nz = g.nz;
     const int z0 = D == 3 ? seg_lo(seg, nz, a.nseg) : 0;
     const int z1 = D == 3 ? seg_lo(seg + 1, nz, a.nseg) : 1;
+    // The planes [zs, ze) of the segment that this workgroup stores, and those
+    // it marches through, [za, zb): with more than one workgroup to a segment,
+    // one plane more on either side inside the segment, collided for the moment
+    // sums of the planes next to it and not stored.  Every sum is then formed
+    // from the same terms in the same order whatever the number of workgroups
+    // (spill layers between them, as between segments, would change the order
+    // and with it the last bits).
+    const int zs = D == 3 ? z0 + seg_lo(nth, z1 - z0, a.nsub) : 0, ze = D == 3 ? z0 + seg_lo(nth + 1, z1 - z0, a.nsub) : 1;
+    const int za = max(zs - 1, z0), zb = min(ze + 1, z1);
 
     // -- z-invariant per-thread set-up ---------------------------------------
     const int lx = tid % TX, ly = tid / TX;
@@ -927,7 +942,7 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
     __shared__ C sRef[2 * Q];
     for (int r = tid; r < 2 * Q; r += NT) sRef[r] = (C)(r < Q ? a.ref.f[r] : a.ref.g[r - Q]);
     // zero columns of the exchange buffers, ring accumulators
-    for (int r = tid; r < 2 * Q; r += NT) sX[r][NT] = S::xenc(C(0));
+    for (int r = tid; r < NX; r += NT) sX[r][NT] = S::xenc(C(0));
     for (int r = tid; r < (D == 3 ? 3 : 1) * 5 * TL::NR; r += NT) (&sRacc[0][0][0])[r] = C(0);
 
     // -- pipeline stages -----------------------------------------------------
@@ -1135,12 +1150,15 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
         for (int k = 0; k < 5; k++) acc[q][k] = C(0);
     // inbound slots, layer-major: one resource per layer over every tile's
     // slots (the whole array may exceed what one resource addresses)
-    auto in_rsrc = [&](int layer) { return make_rsrc(a.INo + (size_t)layer * in_layer, in_layer * (unsigned)sizeof(C)); };
+    auto in_rsrc = [&](int layer, unsigned bytes) { return make_rsrc(a.INo + (size_t)layer * in_layer, bytes); };
     // write plane p (own: acc[0]) to `layer`, then clear its ring slot; the
-    // reference sums enter once per cell, with the tile-own part of its plane
+    // reference sums enter once per cell, with the tile-own part of its plane.
+    // A plane that another workgroup writes goes to resources of no bytes, which
+    // drop the stores.
     auto flush = [&](int p, int layer) {
+        const bool mine = (p >= zs && p < ze) || (p == z0 - 1 && zs == z0) || (p == z1 && ze == z1);
         if (own) {
-            const Rsrc mo = mc_layer(a.Mco, layer);
+            const Rsrc mo = make_rsrc(a.Mco + (long long)layer * 5 * plane, mine ? mc_bytes : 0u);
             const bool plane_layer = D == 2 || layer < nz;
 #pragma unroll
             for (int k = 0; k < 5; k++) {
@@ -1152,7 +1170,7 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
         }
         if (ring) {
             C *ra = &sRacc[s3(p)][0][0];
-            const Rsrc rIN = in_rsrc(layer);
+            const Rsrc rIN = in_rsrc(layer, mine ? in_layer * (unsigned)sizeof(C) : 0u);
 #pragma unroll
             for (int k = 0; k < 5; k++) {
                 if (ring_dst)
@@ -1231,9 +1249,8 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
             if (w & 2) ra[4 * TL::NR + rid] += sg;
         }
     };
-    using WFG = std::integral_constant<int, 3>;
 
-    // -- prologue: rho(z0-3 .. z0+4), L(z0-2 .. z0+2), fields of z0-1, z0 -----
+    // -- prologue: rho(za-3 .. za+4), L(za-2 .. za+2), fields of za-1, za -----
     CenterF<C> Zc, Zm4;  // centre fields of plane z; plane z-1 (u_z, T, h, Lambda_z used)
     constexpr int NJ = MLP ? 6 : 4;  // j, G (and T, accepted flag of the surrogate form) per cell
     C jo[NJ], jr[NJ];
@@ -1251,40 +1268,43 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
         if (D == 3) {
             // four rho slots: each plane is overwritten once its last reader
             // has passed a barrier
-            for (int p = z0 - 3; p <= z0; p++) {
+            {   // four planes in flight
+                C r4[4][NR3], s4r[4][FOLD ? NR3 : 1][3];
+#pragma unroll
+                for (int q = 0; q < 4; q++) load_rho_regs(za - 3 + q, r4[q], s4r[q]);
+#pragma unroll
+                for (int q = 0; q < 4; q++) store_rho(za - 3 + q, r4[q], s4r[q]);
+            }
+            load_rho_regs(za + 1, rv, rvs);  // ahead of the Laplacians
+            __syncthreads();
+            make_lap(za - 2);
+            make_lap(za - 1);
+            __syncthreads();
+            store_rho(za + 1, rv, rvs);
+            load_acc(za - 1, wo, wr);
+            load_jg_now(za - 1);
+            load_acc(za, wo, wr);
+            __syncthreads();
+            make_lap(za);
+            __syncthreads();
+            make_fields(za - 1, jo, jr, Zm4);
+            __syncthreads();
+            for (int p = za + 2; p <= za + 3; p++) {
                 load_rho_regs(p, rv, rvs);
                 store_rho(p, rv, rvs);
             }
+            load_jg_now(za);
+            load_acc(za + 1, wo, wr);
             __syncthreads();
-            make_lap(z0 - 2);
-            make_lap(z0 - 1);
+            make_lap(za + 1);
+            make_lap(za + 2);
             __syncthreads();
-            load_rho_regs(z0 + 1, rv, rvs);
-            store_rho(z0 + 1, rv, rvs);
-            load_acc(z0 - 1, wo, wr);
-            load_jg_now(z0 - 1);
-            load_acc(z0, wo, wr);
+            make_fields(za, jo, jr, Zc);
+            load_jg_now(za + 1);
+            load_acc(za + 2, wo, wr);
+            load_rho_regs(za + 4, rv, rvs);
             __syncthreads();
-            make_lap(z0);
-            __syncthreads();
-            make_fields(z0 - 1, jo, jr, Zm4);
-            __syncthreads();
-            for (int p = z0 + 2; p <= z0 + 3; p++) {
-                load_rho_regs(p, rv, rvs);
-                store_rho(p, rv, rvs);
-            }
-            load_jg_now(z0);
-            load_acc(z0 + 1, wo, wr);
-            __syncthreads();
-            make_lap(z0 + 1);
-            make_lap(z0 + 2);
-            __syncthreads();
-            make_fields(z0, jo, jr, Zc);
-            load_jg_now(z0 + 1);
-            load_acc(z0 + 2, wo, wr);
-            load_rho_regs(z0 + 4, rv, rvs);
-            __syncthreads();
-            store_rho(z0 + 4, rv, rvs);
+            store_rho(za + 4, rv, rvs);
         } else {
             load_rho_regs(0, rv, rvs);
             store_rho(0, rv, rvs);
@@ -1325,9 +1345,9 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
             gq[i] = S::load(&rawg, 0, sRef[Q + i]);
         }
     };
-    load_pops(z0);
+    load_pops(za);
 
-    for (int z = z0; z < z1; z++) {
+    for (int z = za; z < zb; z++) {
         // -- prefetch of rho(z+5) and j, G(z+2); phase A: L(z+3), fields of
         //    plane z+1 ------------------------------------------------------------
         C rv[NR3], jon[NJ], jrn[NJ];
@@ -1407,7 +1427,9 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
         {
             constexpr unsigned PB = 2 * sizeof(T);  // bytes of an (f, g) pair
             const long long pb = 2 * (long long)(D == 3 ? z : 0) * Q * plane;
-            const Rsrc ro = make_rsrc(a.fo + pb, (unsigned)((long long)Q * plane * PB));
+            // (a plane that another workgroup stores: a resource of no bytes)
+            const bool mine = z >= zs && z < ze;
+            const Rsrc ro = make_rsrc(a.fo + pb, mine ? (unsigned)((long long)Q * plane * PB) : 0u);
 #pragma unroll
             for (int i = 0; i < Q; i++) {
                 const C rf_i = sRef[i], rg_i = sRef[Q + i];
@@ -1431,11 +1453,16 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
             }
         };
         xwrite(f, 0);
+        if constexpr (TURN) {
+            __syncthreads();
+            rounds(std::integral_constant<int, 1>{});
+            __syncthreads();
+        }
         xwrite(gq, GROW);
-        if (D == 3 && z + 1 < z1) load_pops(z + 1);
+        if (D == 3 && z + 1 < zb) load_pops(z + 1);
         if (D == 3) load_jg_slots(z + 2, jos, jrs);  // FOLD (live across the gather, not the collision)
         __syncthreads();
-        rounds(WFG{});
+        rounds(std::integral_constant<int, TURN ? 2 : 3>{});
         if (D == 3) {
             flush(z - 1, z == z0 ? nz + 2 * seg : z - 1);  // plane z-1 is complete
             shift_acc();
@@ -1449,7 +1476,7 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
             flush(0, 0);
         }
     }
-    if (D == 3) {
+    if (D == 3 && ze == z1) {
         flush(z1 - 1, z1 - 1);
         shift_acc();
         flush(z1, nz + 2 * seg + 1);

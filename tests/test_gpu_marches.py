@@ -1,0 +1,62 @@
+"""How a tile's march through z is shared out must not show in the result.
+
+* Where tiles and segments leave compute units without work, several workgroups
+  share a segment; every moment sum keeps its terms and their order.  A lattice
+  of one 64-cell period along x (few tiles: shared) and the same state repeated
+  160 times along x (enough tiles: not shared) therefore agree bitwise.
+* FP64 chooses its own number of segments there: parity with the oracle element
+  by element on lattices of a few planes per workgroup.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2510_14712_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+ST = inputs.states()
+KW = inputs.physics(ST, "tgv_3d_512")
+RHOC, T0 = ST["critical"]["rho"], 1.1 * ST["critical"]["T"]
+
+
+@pytest.mark.parametrize("storage,eos,bcy,nz,nseg", [
+    ("f32", "vdw", 0, 13, 1), ("f32", "vdw", 1, 12, 2), ("bf16", "vdw", 0, 13, 2), ("f16", "vdw", 1, 7, 1),
+    ("bf16", "mlp", 0, 14, 2), ("f32", "mlp", 1, 3, 1),
+])
+def test_shared_marches_keep_every_bit(storage, eos, bcy, nz, nseg):
+    from paper_2510_14712_amd import lbm
+    lbm.load()
+    nx, ny, reps = 64, 8, 160
+    print(f"case {storage} {eos} bc_y {bcy} nz {nz} segments {nseg}", flush=True)
+    rho, u, T = inputs.random_state(3, (nx, ny, nz), 31, RHOC, T0, drho=0.03, du=0.05, dT=0.02, white=0.005)
+    kw = dict(bc=(0, bcy, 0), storage=storage, eos=eos, mlp_tol=1e-6, zsegments=nseg, ref_rho=RHOC, ref_T=T0, **KW)
+    net = None
+    if eos == "mlp":
+        box = ST["shock_drop_3d"]["mlp_box"]
+        net = lbm.mlp_train([*box["rho"], *box["T"]], 16384, 9, 2, 4096, 3e-3, inputs.mlp_params(9).astype(np.float32))
+    out = []
+    for k in (1, reps):
+        wide = [np.tile(a.reshape(-1, nz, ny, nx), (1, 1, 1, k)).reshape(-1) for a in (rho, u, T)]
+        with lbm.Lattice(3, (nx * k, ny, nz), **kw) as lat:
+            if net is not None:
+                lat.mlp_set(net[0], net[1])
+            lat.init(*wide).step(5)
+            out.append([t.view(27, nz, ny, nx * k)[..., :nx].cpu().numpy() for t in lat.get_populations()])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("shape,bc", [((33, 9, 5), (0, 0, 0)), ((40, 20, 26), (1, 0, 0)), ((8, 8, 1), (0, 0, 0)), ((64, 17, 31), (0, 1, 0))])
+def test_fp64_short_segments_match_oracle(shape, bc):
+    from paper_2510_14712_amd import lbm
+    lbm.load()
+    kw = inputs.physics(ST)
+    rho, u, T = inputs.random_state(3, shape, 33, RHOC, T0, drho=0.03, du=0.05, dT=0.02, white=0.005)
+    print(f"case {shape} bc={bc}", flush=True)
+    with lbm.Lattice(3, shape, bc=bc, storage="f64", **kw) as lat:
+        f, g = (t.cpu().numpy() for t in lat.init(rho, u, T).step(8).get_populations())
+    p = oracle.Params(3, shape, bc=bc, **kw)
+    fr, gr = oracle.run(p, *oracle.init(p, rho, u, T), 8)
+    assert np.max(np.abs(f - fr)) <= 1e-12 * np.abs(fr).max()
+    assert np.max(np.abs(g - gr)) <= 1e-12 * np.abs(gr).max()

@@ -336,26 +336,16 @@ template <int D, class S> struct Impl {
         using TL = TileOf<S, M>;
         if (!c->mc_pending) return;
         const int nxt = 1 - c->mcc;
-        if (fold(c)) {
-            if (D == 3) {
-                const long long plane = (long long)c->p.nx * c->p.ny;
-                hipLaunchKernelGGL((k_fused_fixup<D, TL, C>), dim3((unsigned)((plane + BX - 1) / BX), 2 * c->nseg),
-                                   dim3(BX), 0, c->stream, c->grid, c->ntx, c->nty, c->nseg, 1,
-                                   (C *)c->Mc[nxt], (const C *)c->IN[nxt]);
-            }
-            return;
-        }
-        const long long per = (long long)c->ntx * c->nty * TL::PMAX;
-        if (!kfold(c))
-            hipLaunchKernelGGL((k_fused_fixup<D, TL, C>), dim3((unsigned)((per + BX - 1) / BX), c->p.nz), dim3(BX),
-                               0, c->stream, c->grid, c->ntx, c->nty, c->nseg, 0, (C *)c->Mc[nxt],
+        const int rows0 = fold(c) || kfold(c) ? 0 : c->p.nz, ends = D == 3 ? 2 * c->nseg : 0;
+        if (rows0 + ends > 0) {
+            const long long per = rows0 ? (long long)c->ntx * c->nty * TL::PMAX : 0;
+            const long long plane = ends ? (long long)c->p.nx * c->p.ny : 0;
+            hipLaunchKernelGGL((k_fused_fixup<D, TL, C>),
+                               dim3((unsigned)((std::max(per, plane) + BX - 1) / BX), (unsigned)(rows0 + ends)), dim3(BX),
+                               0, c->stream, c->grid, c->ntx, c->nty, c->nseg, rows0, (C *)c->Mc[nxt],
                                (const C *)c->IN[nxt]);
-        if (D == 3) {
-            const long long plane = (long long)c->p.nx * c->p.ny;
-            hipLaunchKernelGGL((k_fused_fixup<D, TL, C>), dim3((unsigned)((plane + BX - 1) / BX), 2 * c->nseg),
-                               dim3(BX), 0, c->stream, c->grid, c->ntx, c->nty, c->nseg, 1,
-                               (C *)c->Mc[nxt], (const C *)c->IN[nxt]);
         }
+        if (fold(c)) return;
         c->mcc = nxt;
         c->mc_pending = false;
     }
@@ -364,17 +354,7 @@ template <int D, class S> struct Impl {
     static void fused_eos(lbm_ctx *c) {
         if constexpr (std::is_same<C, float>::value) {
             if (!mlp(c)) return;
-            // 64 x 4 columns per workgroup, marching through the fewest chunks
-            // of at most 58 planes, as even as nz allows (longer chunks spread
-            // the prologue -- rho region of four planes, two Laplacians, the
-            // permuted weights -- over more planes: at 512^3, 32 -> 56 took the
-            // pass 2.98 -> 2.88 ms, nine chunks of 57 and 56 instead of nine of
-            // 56 and one of 8 2.39 -> 2.36 ms; the end-plane bitmask of the
-            // completing pass spans a chunk plus 6 planes, at most 64)
-            constexpr int ZCHUNK_MAX = 58;
-            static_assert(ZCHUNK_MAX + 6 <= 64, "end-plane bitmask of the surrogate pass");
-            const int nchunk = D == 3 ? (c->p.nz + ZCHUNK_MAX - 1) / ZCHUNK_MAX : 1;
-            const int zchunk = D == 3 ? (c->p.nz + nchunk - 1) / nchunk : 1;
+            const int zchunk = c->zchunk;
             const dim3 grid((unsigned)((c->p.nx + 63) / 64), (unsigned)((c->p.ny + 3) / 4),
                             (unsigned)((c->p.nz + zchunk - 1) / zchunk));
             FoldArgs fa{nullptr, nullptr, c->ntx, c->nty, c->nseg};
@@ -754,6 +734,7 @@ template <int D, class S> struct Impl {
     static void tiles(lbm_ctx *c) {
         mlp(c) ? tiles_t<true>(c) : tiles_t<false>(c);
         c->folded = fold(c);
+        c->zchunk = eos_chunk(c);
     }
     // Resident workgroups of the fused step: compute units x the kernel's
     // occupancy (the instance the step launches); 0 if the device cannot be
@@ -786,6 +767,32 @@ template <int D, class S> struct Impl {
         for (int m = 2; m <= planes; m++)
             if (cost(m) < cost(best)) best = m;
         return cost(best) * 20 <= cost(1) * 19 ? best : 1;
+    }
+    // Planes per workgroup of the surrogate pass.  64 x 4 columns march through
+    // the fewest chunks of at most 58 planes, as even as nz allows (longer chunks
+    // spread the prologue -- rho region of four planes, two Laplacians, the
+    // permuted weights -- over more planes: at 512^3, 32 -> 56 took the pass 2.98
+    // -> 2.88 ms, nine chunks of 57 and 56 instead of nine of 56 and one of 8
+    // 2.39 -> 2.36 ms; the end-plane bitmask of the completing pass spans a chunk
+    // plus 6 planes, at most 64).  Where these leave compute units without work
+    // (two workgroups each), the count with the shortest march and its prologue of
+    // about five planes; a cell's value does not depend on its chunk.
+    static int eos_chunk(const lbm_ctx *c) {
+        constexpr int ZCHUNK_MAX = 58;
+        static_assert(ZCHUNK_MAX + 6 <= 64, "end-plane bitmask of the surrogate pass");
+        const int nz = c->p.nz;
+        if (D == 2) return 1;
+        int n = (nz + ZCHUNK_MAX - 1) / ZCHUNK_MAX, dev = 0, ncu = 0;
+        const long long cols = (long long)((c->p.nx + 63) / 64) * ((c->p.ny + 3) / 4);
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1) {
+            (void)hipGetLastError();
+        } else if (cols * n < 2 * ncu) {
+            auto march = [&](int k) { return ((cols * k + 2 * ncu - 1) / (2 * ncu)) * ((nz + k - 1) / k + 5); };
+            for (int k = n + 1; k <= nz; k++)
+                if (march(k) < march(n)) n = k;
+        }
+        return (nz + n - 1) / n;
     }
     template <bool M> static void tiles_t(lbm_ctx *c) {
         using TL = TileOf<S, M>;

@@ -1485,18 +1485,24 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
 
 // Completes the moments of the output state: adds the inbound slots of tile
 // edge cells and the spill layers of the segment end planes into Mc (own
-// layers).  mode 0: perimeter cells of tiles in planes that are not segment
-// ends, grid (ceil(tiles * PMAX / BX), nz); mode 1 (D = 3): every cell of the
-// first and last plane of each segment, grid (ceil(nx ny / BX), 2 nseg).
+// layers).  Block rows y < nrows0: the perimeter cells of the tiles in plane y,
+// unless it is a segment end (nrows0 = nz, or 0 where the next step completes
+// them); rows from nrows0 on (D = 3): every cell of the first and last plane of
+// each segment.  One launch for both: on small lattices a second one cost as
+// much as the work.
+//
+// A thread's loads are issued together before its sums, one memory round trip
+// instead of one per moment.
 template <int D, class TL, class C>
-__global__ void __launch_bounds__(BX) k_fused_fixup(Grid g, int ntx, int nty, int nseg, int mode,
+__global__ void __launch_bounds__(BX) k_fused_fixup(Grid g, int ntx, int nty, int nseg, int nrows0,
                                                     C *__restrict__ Mc, const C *__restrict__ IN) {
     // 32-bit index arithmetic throughout (tiles x perimeter slots, planes and
     // layers all fit); the z plane and its segment are uniform per block
     const int nz = g.nz;
-    int z, s = 0;
+    const bool ends = (int)blockIdx.y >= nrows0;
+    int z, s = 0, zlo = 0, zhi = 0;
     int gxv, gyv;
-    if (mode == 0) {
+    if (!ends) {
         z = blockIdx.y;
         if (D == 3) {
             s = seg_of(z, nz, nseg);
@@ -1523,10 +1529,12 @@ __global__ void __launch_bounds__(BX) k_fused_fixup(Grid g, int ntx, int nty, in
         gxv = tx * TL::TX + lx;
         gyv = ty * TL::TY + ly;
     } else {
-        s = blockIdx.y >> 1;
-        const int zlo = seg_lo(s, nz, nseg), zhi = seg_lo(s + 1, nz, nseg) - 1;
-        if ((blockIdx.y & 1) && zhi == zlo) return;
-        z = (blockIdx.y & 1) ? zhi : zlo;
+        const int e = (int)blockIdx.y - nrows0;
+        s = e >> 1;
+        zlo = seg_lo(s, nz, nseg);
+        zhi = seg_lo(s + 1, nz, nseg) - 1;
+        if ((e & 1) && zhi == zlo) return;
+        z = (e & 1) ? zhi : zlo;
         const unsigned c = blockIdx.x * (unsigned)BX + threadIdx.x;
         if (c >= (unsigned)g.nx * (unsigned)g.ny) return;
         gxv = (int)(c % (unsigned)g.nx);
@@ -1535,6 +1543,7 @@ __global__ void __launch_bounds__(BX) k_fused_fixup(Grid g, int ntx, int nty, in
     const int tx = gxv / TL::TX, ty = gyv / TL::TY;
     const int lx = gxv - tx * TL::TX, ly = gyv - ty * TL::TY;
     const int w = min(TL::TX, g.nx - tx * TL::TX), h = min(TL::TY, g.ny - ty * TL::TY);
+    const bool edge = lx == 0 || lx == w - 1 || ly == 0 || ly == h - 1;
     const unsigned tile = (unsigned)(ty * ntx + tx);
     const unsigned plane = (unsigned)g.nx * (unsigned)g.ny;
     const unsigned cell = (unsigned)gxv + (unsigned)g.nx * (unsigned)gyv;
@@ -1542,35 +1551,39 @@ __global__ void __launch_bounds__(BX) k_fused_fixup(Grid g, int ntx, int nty, in
     auto mc = [&](int layer, int k) -> C & { return Mc[(size_t)(layer * 5 + k) * plane + cell]; };
     // inbound slots, layer-major [nlay][tiles][5][NR]
     const unsigned ntile = (unsigned)(ntx * nty);
-    auto in = [&](int layer, int k) {
-        return IN + (size_t)layer * ntile * 5u * TL::NR + ((size_t)tile * 5u + (unsigned)k) * TL::NR;
-    };
-    if (D == 3 && mode == 1) {
-        const int zlo = seg_lo(s, nz, nseg), zhi = seg_lo(s + 1, nz, nseg) - 1;
-        const int lay_hi = nz + 2 * ((s + nseg - 1) % nseg) + 1;  // plane z0 of segment s, from segment s-1
-        const int lay_lo = nz + 2 * ((s + 1) % nseg);             // plane z1-1 of segment s, from segment s+1
-        for (int k = 0; k < 5; k++) {
-            C v = mc(z, k) + inbound_sum<TL>(in(z, k), lx, ly, w, h);
-            if (z == zlo) v += mc(lay_hi, k) + inbound_sum<TL>(in(lay_hi, k), lx, ly, w, h);
-            if (z == zhi) v += mc(lay_lo, k) + inbound_sum<TL>(in(lay_lo, k), lx, ly, w, h);
-            mc(z, k) = v;
-        }
-    } else {
-        // all loads of the cell first, then the stores: one memory round trip
-        // per thread instead of one per moment
-        C v[5];
+    // a layer's own part and inbound slots of the cell
+    auto part = [&](int layer, C(&v)[5]) {
+        const C *in = IN + (size_t)layer * ntile * 5u * TL::NR + (size_t)tile * 5u * TL::NR;
 #pragma unroll
-        for (int k = 0; k < 5; k++) v[k] = mc(z, k);
+        for (int k = 0; k < 5; k++) v[k] = mc(layer, k);
+        if (!edge) return;
         if (w >= 2 && h >= 2) {
 #pragma unroll
-            for (int k = 0; k < 5; k++) v[k] += inbound_sum_2x2<TL>(in(z, k), lx, ly, w, h);
+            for (int k = 0; k < 5; k++) v[k] += inbound_sum_2x2<TL>(in + k * TL::NR, lx, ly, w, h);
         } else {
 #pragma unroll
-            for (int k = 0; k < 5; k++) v[k] += inbound_sum<TL>(in(z, k), lx, ly, w, h);
+            for (int k = 0; k < 5; k++) v[k] += inbound_sum<TL>(in + k * TL::NR, lx, ly, w, h);
         }
+    };
+    C v[5];
+    part(z, v);
+    if (D == 3 && ends) {
+        // plane z0 of segment s receives from segment s-1, plane z1-1 from segment s+1
+        if (z == zlo) {
+            C t[5];
+            part(nz + 2 * ((s + nseg - 1) % nseg) + 1, t);
 #pragma unroll
-        for (int k = 0; k < 5; k++) mc(z, k) = v[k];
+            for (int k = 0; k < 5; k++) v[k] += t[k];
+        }
+        if (z == zhi) {
+            C t[5];
+            part(nz + 2 * ((s + 1) % nseg), t);
+#pragma unroll
+            for (int k = 0; k < 5; k++) v[k] += t[k];
+        }
     }
+#pragma unroll
+    for (int k = 0; k < 5; k++) mc(z, k) = v[k];
 }
 
 // Complete moments rho, J, G of every cell into the field arrays, for a

@@ -49,7 +49,7 @@ struct lbm_ctx {
     // small D2Q9 lattices: several steps in one launch (0 threads: not)
     int b2_threads = 0, b2_own = 0, b2_halo = 0, b2_steps = 0;
     size_t mc_bytes = 0, in_bytes = 0;
-    int ntx = 0, nty = 0, nseg = 1, nsub = 1, nlay = 0, chunk = 0;
+    int ntx = 0, nty = 0, nseg = 1, nsub = 1, nlay = 0, chunk = 0, zchunk = 1;
 };
 
 // equation-of-state modes

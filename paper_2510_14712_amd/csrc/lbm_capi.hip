@@ -262,8 +262,9 @@ template <int D, class S> struct Impl {
     }
     // full tiles and periodic x, y: the instance without wall and
     // partial-tile handling.  With 16-bit storage and the explicit EOS that
-    // instance also completes its input moments itself (kfold) and needs z
-    // segments of at least 6 planes; shorter ones take the general instance.
+    // instance also completes its input moments itself (kfold) and on D3Q27
+    // needs z segments of at least 6 planes; shorter ones take the general
+    // instance.
     static constexpr bool fold_storage = sizeof(T) == 2;
     template <bool M> static bool fast_instance(const lbm_ctx *c) {
         using TL = TileOf<S, M>;
@@ -272,7 +273,12 @@ template <int D, class S> struct Impl {
         if (!fast || M || !fold_storage || D == 2) return fast;
         return c->p.nz / c->nseg >= 6;
     }
-    static bool kfold(const lbm_ctx *c) { return fold_storage && !mlp(c) && c->fused && fast_instance<false>(c); }
+    // D2Q9: every instance, on tiles of at least 2 x 2 cells
+    static bool kfold(const lbm_ctx *c) {
+        using TL = TileOf<S, false>;
+        if (mlp(c) || !c->fused || c->b2_threads) return false;
+        return D == 2 ? c->p.nx % TL::TX != 1 && c->p.ny % TL::TY != 1 : fold_storage && fast_instance<false>(c);
+    }
     // the fused step proper (kind 0 of step_timed)
     static void fused_main(lbm_ctx *c) { mlp(c) ? fused_main_t<true>(c) : fused_main_t<false>(c); }
     template <bool M> static void fused_main_t(lbm_ctx *c) {
@@ -285,6 +291,7 @@ template <int D, class S> struct Impl {
         a.nty = c->nty;
         a.nseg = c->nseg;
         a.nsub = c->nsub;
+        a.fold = kfold(c) ? 1 : 0;
         a.nlay = c->nlay;
         a.chunk = c->chunk;
         a.pull = c->pulled;
@@ -1002,6 +1009,8 @@ int lbm_create(const lbm_params *params, lbm_ctx **out) {
     if (!c->fused) c->folded = false;
     auto plan2d = [&]() { DISPATCH_VOID(c, block2d_plan(c)); };
     plan2d();
+    auto kfolded = [&]() -> bool { DISPATCH(c, kfold(c)); };
+    c->kfolded = kfolded();
     // field arrays: rho, J[D], G, lap (all that a read-back of the fused path
     // uses); the multi-kernel path's also u[D], F[D], Lam[D], T, P, h, cs2, with
     // Peng-Robinson e(rho, T), and the four shock-capturing work arrays when
@@ -1148,7 +1157,7 @@ const char *lbm_kernel_name(const lbm_ctx *c, int k) {
     if (c && c->b2_threads) return k == 0 ? "k_block2d" : "";
     if (c && c->fused)  // folded: the surrogate pass does the fix-up's work but on the segment-end planes
         return k == 0 ? "k_fused"
-                      : (k == 1 ? (c->folded && c->p.lattice == 2 ? "" : "k_fused_fixup")
+                      : (k == 1 ? ((c->folded || c->kfolded) && c->p.lattice == 2 ? "" : "k_fused_fixup")
                                 : (k == 2 && c->p.eos == LBM_EOS_MLP ? "k_eos_surrogate" : ""));
     return k >= 0 && k < LBM_NUM_KERNELS ? names[k] : "";
 }

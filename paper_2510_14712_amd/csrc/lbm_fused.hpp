@@ -76,6 +76,7 @@ template <class C, class T> struct FusedArgs {
     Phys<C> ph;
     RefPops ref;
     int ntx, nty, nseg;  // tiles along x, y; z segments
+    int fold;            // D2Q9 with the explicit EOS: 1 when the step completes its input moments itself
     int nsub;            // workgroups that share a tile's march through a segment
     int nlay;            // layers of Mc / IN: nz planes + 2 spill layers per segment (D = 3), 1 (D = 2)
     int chunk;           // tiles per XCD in the remapped order, 0: identity order
@@ -169,9 +170,12 @@ __device__ __forceinline__ C inbound_sum_2x2(const C *in, int lx, int ly, int w,
 // global coordinate along an axis for a tile-relative offset, and the
 // effective tile-relative offset at which a field is evaluated (ghost cells of
 // zero-gradient axes take the clamped cell's value)
+// (t0 < n, -3 <= rel <= 66: on a lattice of at least 70 cells one addition or
+// subtraction wraps; the division of shorter ones is some 40 instructions)
 __device__ __forceinline__ int axis_global(int t0, int rel, int n, int clamp) {
     int v = t0 + rel;
     if (clamp) return v < 0 ? 0 : (v >= n ? n - 1 : v);
+    if (n >= 70) return v < 0 ? v + n : (v >= n ? v - n : v);
     v %= n;
     return v < 0 ? v + n : v;
 }
@@ -775,17 +779,19 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
         g.clampx = 0;
         g.clampy = 0;
     }
-    // FOLD (the full-tile periodic instances with 16-bit storage and the
-    // explicit EOS): the input side channel holds the previous step's
-    // tile-own partial sums -- complete only on the segment-end planes, which
-    // the fix-up's end-plane launch completes -- and INi its inbound slots.
-    // Every moment read is completed on load with the fix-up's terms, order
-    // and rounding (a perimeter cell adds its side, bottom/top and corner
-    // slot), so the step needs no pass over the tiles' perimeter cells.  The
-    // extra loads cost these instances less than the pass they replace; the
-    // FP32 instance, already at the register limit, ran 30 % slower with them
-    // and keeps the separate fix-up.
-    constexpr bool FOLD = FAST && !MLP && sizeof(T) == 2;
+    // FOLD (D2Q9, and on D3Q27 the full-tile periodic instances with 16-bit
+    // storage; the explicit EOS): the input side channel holds the previous
+    // step's tile-own partial sums -- complete only on the segment-end planes,
+    // which the fix-up completes -- and INi its inbound slots.  Every moment
+    // read is completed on load with the fix-up's terms, order and rounding (a
+    // perimeter cell adds its side, bottom/top and corner slot), so the step
+    // needs no pass over the tiles' perimeter cells.  The extra loads cost these
+    // instances no more than the pass they replace (D2Q9, FP32: 2048 x 1024 cells
+    // 104 us per step either way, 512 x 512 20.5 -> 19.0, 300 x 100, where the
+    // second launch was a third of the step, 12.1 -> 10.8); the FP32 instance on
+    // D3Q27, already at the register limit, ran 30 % slower with them and keeps
+    // the separate fix-up.
+    constexpr bool FOLD = !MLP && (D == 2 || (FAST && sizeof(T) == 2));
     const long long N = g.N;
     const long long plane = (long long)g.nx * g.ny;
     const int tid = threadIdx.x;
@@ -850,7 +856,7 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
     // FOLD: byte offsets (moment 0, within a layer) of the side, bottom/top
     // and corner slot of a lattice cell in its tile's slot array (SLOT_NONE
     // where it has none), and whether it lies on the tile's left/right and
-    // bottom/top edge (full tiles)
+    // bottom/top edge (tiles of at least 2 x 2 cells)
     struct SlotRef {
         unsigned sh, sv, sc;
         bool hs, vs;
@@ -858,7 +864,8 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
     auto slot_ref = [&](int xe, int ye) {
         const int ttx = xe / TX, tty = ye / TY;
         const int ex = xe - ttx * TX, ey = ye - tty * TY;
-        const bool l = ex == 0, r = ex == TX - 1, b = ey == 0, t = ey == TY - 1;
+        const int tw = FAST ? TX : min(TX, g.nx - ttx * TX), th = FAST ? TY : min(TY, g.ny - tty * TY);
+        const bool l = ex == 0, r = ex == tw - 1, b = ey == 0, t = ey == th - 1;
         const unsigned base = (unsigned)(tty * a.ntx + ttx) * 5u * TL::NR;
         SlotRef o;
         o.hs = l || r;
@@ -874,10 +881,11 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
 #pragma unroll
         for (int k = 0; k < NR3; k++) {
             const int r = min(tid + k * NT, TL::R3 - 1);
-            rho_ref[k] = slot_ref(axis_global(x0, r % TL::W3 - 3, g.nx, 0), axis_global(y0, r / TL::W3 - 3, g.ny, 0));
+            rho_ref[k] = slot_ref(axis_global(x0, r % TL::W3 - 3, g.nx, g.clampx),
+                                  axis_global(y0, r / TL::W3 - 3, g.ny, g.clampy));
         }
         own_ref = slot_ref(gx, gy);
-        ring_ref = ring ? slot_ref(axis_global(x0, rx, g.nx, 0), axis_global(y0, ry, g.ny, 0)) : own_ref;
+        ring_ref = ring ? slot_ref(axis_global(x0, rx, g.nx, g.clampx), axis_global(y0, ry, g.ny, g.clampy)) : own_ref;
     }
     // Laplacian on R2: R3 index of the evaluation point
     int lap_c[NR2];
@@ -965,7 +973,7 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
     // [z0 - 3, z1 + 5) meets no other segment's end plane
     const int zend_below = D == 3 ? zwrap(z0 - 1) : -1, zend_above = D == 3 ? zwrap(z1) : -1;
     auto is_end = [&](int p) {
-        if (D != 3) return false;
+        if (D != 3) return a.fold == 0;  // completed by the fix-up: nothing to add
         const int wp = zwrap(p);
         return wp == z0 || wp == z1 - 1 || wp == zend_below || wp == zend_above;
     };
@@ -1250,6 +1258,41 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
         }
     };
 
+    // arrived populations of the own cell of plane p into f, g (loaded one
+    // position ahead, so that their latency overlaps the exchange and the
+    // field pipeline)
+    C f[Q], gq[Q];
+    T f0[D == 2 ? Q : 1], g0[D == 2 ? Q : 1];  // D2Q9: as stored
+    auto load_pops = [&](int p) {
+        // one resource per source plane (c_z = -1, 0, +1 read planes p + 1,
+        // p, p - 1 of the pulled set) over its Q nx ny pairs; uniform offset
+        // of direction i, lane offset of the source cell
+        constexpr unsigned PB = 2 * sizeof(T);  // bytes of an (f, g) pair
+        const unsigned pbytes = (unsigned)((long long)Q * plane * PB);
+        Rsrc rp[3];
+#pragma unroll
+        for (int c = 0; c < (D == 3 ? 3 : 1); c++) {
+            const int ps = D == 3 ? zwrap(p - a.pull * (c - 1)) : 0;
+            rp[c] = make_rsrc(a.fi + 2 * (long long)ps * Q * plane, pbytes);
+        }
+#pragma unroll
+        for (int i = 0; i < Q; i++) {
+            const int c = D == 3 ? cz_of(i) + 1 : 0;
+            const unsigned so = (unsigned)i * (unsigned)plane * PB;
+            const unsigned vo = (xs[cx_of(i) + 1] + ys[cy_of(i) + 1]) * PB;
+            if constexpr (D == 2) {
+                pair_ld(rp[c], vo, so, f0[i], g0[i]);
+                continue;
+            }
+            T rawf, rawg;
+            pair_ld(rp[c], vo, so, rawf, rawg);
+            f[i] = S::load(&rawf, 0, sRef[i]);
+            gq[i] = S::load(&rawg, 0, sRef[Q + i]);
+        }
+    };
+    // one plane only: its loads go out before the prologue's
+    if (D == 2) load_pops(0);
+
     // -- prologue: rho(za-3 .. za+4), L(za-2 .. za+2), fields of za-1, za -----
     CenterF<C> Zc, Zm4;  // centre fields of plane z; plane z-1 (u_z, T, h, Lambda_z used)
     constexpr int NJ = MLP ? 6 : 4;  // j, G (and T, accepted flag of the surrogate form) per cell
@@ -1318,34 +1361,15 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
         __syncthreads();
     }
 
-    // arrived populations of the own cell of plane p into f, g (loaded one
-    // position ahead, so that their latency overlaps the exchange and the
-    // field pipeline)
-    C f[Q], gq[Q];
-    auto load_pops = [&](int p) {
-        // one resource per source plane (c_z = -1, 0, +1 read planes p + 1,
-        // p, p - 1 of the pulled set) over its Q nx ny pairs; uniform offset
-        // of direction i, lane offset of the source cell
-        constexpr unsigned PB = 2 * sizeof(T);  // bytes of an (f, g) pair
-        const unsigned pbytes = (unsigned)((long long)Q * plane * PB);
-        Rsrc rp[3];
-#pragma unroll
-        for (int c = 0; c < (D == 3 ? 3 : 1); c++) {
-            const int ps = D == 3 ? zwrap(p - a.pull * (c - 1)) : 0;
-            rp[c] = make_rsrc(a.fi + 2 * (long long)ps * Q * plane, pbytes);
-        }
+    if constexpr (D == 2) {
 #pragma unroll
         for (int i = 0; i < Q; i++) {
-            const int c = D == 3 ? cz_of(i) + 1 : 0;
-            const unsigned so = (unsigned)i * (unsigned)plane * PB;
-            const unsigned vo = (xs[cx_of(i) + 1] + ys[cy_of(i) + 1]) * PB;
-            T rawf, rawg;
-            pair_ld(rp[c], vo, so, rawf, rawg);
-            f[i] = S::load(&rawf, 0, sRef[i]);
-            gq[i] = S::load(&rawg, 0, sRef[Q + i]);
+            f[i] = S::load(&f0[i], 0, sRef[i]);
+            gq[i] = S::load(&g0[i], 0, sRef[Q + i]);
         }
-    };
-    load_pops(za);
+    } else {
+        load_pops(za);
+    }
 
     for (int z = za; z < zb; z++) {
         // -- prefetch of rho(z+5) and j, G(z+2); phase A: L(z+3), fields of

@@ -45,6 +45,7 @@ struct lbm_ctx {
     // when it does the fix-up's work)
     int mcc = 0;
     bool mc_pending = false;
+    bool kfolded = false;  // the fused step completes its input moments itself
     bool folded = false;  // the surrogate pass completes the side channel (the fix-up only its segment-end planes)
     // small D2Q9 lattices: several steps in one launch (0 threads: not)
     int b2_threads = 0, b2_own = 0, b2_halo = 0, b2_steps = 0;

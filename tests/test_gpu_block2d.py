@@ -75,4 +75,7 @@ def test_larger_lattices_keep_the_step_of_one_launch_each():
     lbm.load()
     rho, u, T = inputs.random_state(2, (256, 65), 58, RHOC, 1.1 * TC)
     with lbm.Lattice(2, (256, 65), storage="f32", **KW) as lat:
-        assert set(lat.init(rho, u, T).step_timed(2)) == {"k_fused", "k_fused_fixup"}
+        assert set(lat.init(rho, u, T).step_timed(2)) == {"k_fused", "k_fused_fixup"}  # 65 = 16 x 4 + 1 rows: one-cell tiles
+    rho, u, T = inputs.random_state(2, (256, 66), 58, RHOC, 1.1 * TC)
+    with lbm.Lattice(2, (256, 66), storage="f32", **KW) as lat:
+        assert set(lat.init(rho, u, T).step_timed(2)) == {"k_fused"}

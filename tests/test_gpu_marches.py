@@ -60,3 +60,31 @@ def test_fp64_short_segments_match_oracle(shape, bc):
     fr, gr = oracle.run(p, *oracle.init(p, rho, u, T), 8)
     assert np.max(np.abs(f - fr)) <= 1e-12 * np.abs(fr).max()
     assert np.max(np.abs(g - gr)) <= 1e-12 * np.abs(gr).max()
+
+
+# D2Q9 lattices beyond the several-steps-per-launch form: the step completes its
+# input moments itself (tiles of at least 2 x 2 cells) or leaves that to the
+# fix-up (65 x 41: one-cell tiles)
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("shape,bc", [((70, 75), (1, 0)), ((70, 78), (0, 1)), ((128, 72), (0, 0)), ((98, 66), (1, 1)), ((65, 73), (1, 0))])
+def test_d2q9_step_completes_its_moments(storage, shape, bc):
+    from paper_2510_14712_amd import lbm
+    lbm.load()
+    kw = inputs.physics(ST)
+    rho, u, T = inputs.random_state(2, shape, 35, RHOC, T0, drho=0.03, du=0.05, dT=0.02, white=0.005)
+    print(f"case {storage} {shape} bc={bc}", flush=True)
+    with lbm.Lattice(2, shape, bc=bc + (0,), storage=storage, **kw) as a, \
+            lbm.Lattice(2, shape, bc=bc + (0,), storage=storage, **kw) as b:
+        assert "k_fused" in a.init(rho, u, T).step_timed(4)
+        a.step(2)
+        b.set_populations(*a.get_populations())
+        for lat in (a, b):
+            lat.step(3)
+        pops = [[t.cpu().numpy() for t in lat.get_populations()] for lat in (a, b)]
+    # a restart recomputes the complete moments from the populations
+    assert np.array_equal(pops[0][0], pops[1][0]) and np.array_equal(pops[0][1], pops[1][1])
+    if storage == "f64":
+        p = oracle.Params(2, shape, bc=bc + (0,), **kw)
+        fr, gr = oracle.run(p, *oracle.init(p, rho, u, T), 9)
+        assert np.max(np.abs(pops[0][0] - fr)) <= 1e-12 * np.abs(fr).max()
+        assert np.max(np.abs(pops[0][1] - gr)) <= 1e-12 * np.abs(gr).max()

@@ -138,10 +138,6 @@ static dim3 flat_grid(const lbm_ctx *c) {
     return dim3((unsigned)((plane + BX - 1) / BX), (unsigned)c->p.nz);
 }
 
-static dim3 cell_grid(const lbm_ctx *c) {
-    return dim3((unsigned)((c->p.nx + BX - 1) / BX), (unsigned)c->p.ny, (unsigned)c->p.nz);
-}
-
 static thread_local char g_last_error[256] = "";
 
 int lbm_note(hipError_t e) {
@@ -486,7 +482,7 @@ template <int D, class S> struct Impl {
         *fS = *fs = nullptr;
         if (!c->sc) return;
         Fields<C> fl = get_fields<C>(c);
-        const dim3 gr = cell_grid(c);
+        const dim3 gr = flat_grid(c);
         hipLaunchKernelGGL((k_sc_grad<D, C>), gr, dim3(BX), 0, c->stream, c->grid, make_phys<C>(c->p), fl);
         hipLaunchKernelGGL((k_sc_d4<D, C>), gr, dim3(BX), 0, c->stream, c->grid, fl.sc[0], fl.sc[1], fl.sc[2],
                            fl.sc[3]);

@@ -169,16 +169,17 @@ __global__ void __launch_bounds__(BX, 2) k_cells_mlp(Grid g, Phys<float> ph, Mom
         bool fb;
         if (ph.pr) {
             const double rd = (double)rho, ed = (double)e;
-            EosPoint q = pr_eos(ph, rd, (double)T);
+            const double L = pr_log(ph, rd);
+            EosPoint q = pr_eos(ph, rd, (double)T, L);
             fb = !(fabs(q.e - ed) <= (double)tol * q.cv * fabs((double)T));
             if (fb) {
                 int it = 0;
-                const double Td = pr_temperature(ph, rd, ed, (double)T, it);
-                q = pr_eos(ph, rd, Td);
+                const double Td = pr_temperature(ph, rd, ed, (double)T, L, it);
+                q = pr_eos(ph, rd, Td, L);
                 T = (float)Td;
                 n_it += active ? (unsigned)it : 0u;
             }
-            if (MODE == MLP_STEP) ec = (float)pr_eos(ph, rd, (double)T).e;
+            if (MODE == MLP_STEP) ec = (float)pr_eos(ph, rd, (double)T, L).e;
             Pr = (float)q.P;
             c2 = (float)q.cs2;
         } else {

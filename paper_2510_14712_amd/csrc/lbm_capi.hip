@@ -340,13 +340,19 @@ template <int D, class S> struct Impl {
         if (!c->mc_pending) return;
         const int nxt = 1 - c->mcc;
         const int rows0 = fold(c) || kfold(c) ? 0 : c->p.nz, ends = D == 3 ? 2 * c->nseg : 0;
-        if (rows0 + ends > 0) {
-            const long long per = rows0 ? (long long)c->ntx * c->nty * TL::PMAX : 0;
-            const long long plane = ends ? (long long)c->p.nx * c->p.ny : 0;
-            hipLaunchKernelGGL((k_fused_fixup<D, TL, C>),
-                               dim3((unsigned)((std::max(per, plane) + BX - 1) / BX), (unsigned)(rows0 + ends)), dim3(BX),
-                               0, c->stream, c->grid, c->ntx, c->nty, c->nseg, rows0, (C *)c->Mc[nxt],
+        const long long per = (long long)c->ntx * c->nty * TL::PMAX, plane = (long long)c->p.nx * c->p.ny;
+        // rows of the perimeter cells, then of the segment ends
+        auto launch = [&](int rows, int erows) {
+            const long long n = std::max(rows ? per : 0, erows ? plane : 0);
+            hipLaunchKernelGGL((k_fused_fixup<D, TL, C>), dim3((unsigned)((n + BX - 1) / BX), (unsigned)(rows + erows)),
+                               dim3(BX), 0, c->stream, c->grid, c->ntx, c->nty, c->nseg, rows, (C *)c->Mc[nxt],
                                (const C *)c->IN[nxt]);
+        };
+        if (rows0 + ends > 65535) {  // beyond a grid's second extent (lattices of more than about 60000 planes)
+            launch(rows0, 0);
+            launch(0, ends);
+        } else if (rows0 + ends > 0) {
+            launch(rows0, ends);
         }
         if (fold(c)) return;
         c->mcc = nxt;

@@ -88,3 +88,24 @@ def test_d2q9_step_completes_its_moments(storage, shape, bc):
         fr, gr = oracle.run(p, *oracle.init(p, rho, u, T), 9)
         assert np.max(np.abs(pops[0][0] - fr)) <= 1e-12 * np.abs(fr).max()
         assert np.max(np.abs(pops[0][1] - gr)) <= 1e-12 * np.abs(gr).max()
+
+
+def test_planes_up_to_the_limit():
+    """65535 planes: perimeter rows and segment ends together exceed a grid's
+    second extent.  A state uniform along z gives the planes of a short lattice,
+    to the rounding of sums that the segments order differently (1e-12)."""
+    from paper_2510_14712_amd import lbm
+    lbm.load()
+    nx, ny, nz = 8, 4, 65535
+    print(f"case {nx} x {ny} x {nz}", flush=True)
+    rho, u, T = inputs.random_state(2, (nx, ny), 35, RHOC, T0, drho=0.03, du=0.05, dT=0.02, white=0.005)
+    u = np.concatenate([u.reshape(2, -1), np.zeros((1, nx * ny))])
+    out = []
+    for n in (8, nz):
+        tall = [np.ascontiguousarray(np.broadcast_to(a[:, None], (a.shape[0], n, nx * ny))).reshape(-1)
+                for a in (rho.reshape(1, -1), u, T.reshape(1, -1))]
+        with lbm.Lattice(3, (nx, ny, n), storage="f64", **inputs.physics(ST)) as lat:
+            assert lat.fused
+            out.append([p.view(27, n, nx * ny).cpu() for p in lat.init(*tall).step(3).get_populations()])
+    for a, b in zip(*out):
+        assert float((b - a[:, :1]).abs().max()) <= 1e-12 * float(a.abs().max())

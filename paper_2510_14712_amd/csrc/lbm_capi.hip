@@ -603,8 +603,13 @@ template <int D, class S> struct Impl {
     }
     static int block2d_step(lbm_ctx *c, int n) {
         const long long every = c->p.check_every;
-        while (n > 0) {
-            int k = std::min(n, c->b2_steps);
+        // As many launches, or one more, as turn the two buffers like n single
+        // steps would: a captured call of an even number of steps ends in the
+        // buffer it began in and can be replayed, as on the other paths.
+        int launches = (n + c->b2_steps - 1) / c->b2_steps;
+        if ((launches ^ n) & 1) launches++;
+        for (; n > 0; launches--) {
+            int k = every > 0 ? std::min(n, c->b2_steps) : (n + launches - 1) / launches;
             if (every > 0) k = (int)std::min<long long>(k, every - c->steps_done % every);
             block2d_launch(c, k);
             int rc = last_launch();

@@ -79,3 +79,32 @@ def test_larger_lattices_keep_the_step_of_one_launch_each():
     rho, u, T = inputs.random_state(2, (256, 66), 58, RHOC, 1.1 * TC)
     with lbm.Lattice(2, (256, 66), storage="f32", **KW) as lat:
         assert set(lat.init(rho, u, T).step_timed(2)) == {"k_fused"}
+
+
+@pytest.mark.parametrize("shape,bc,steps", [((64, 4), (0, 0), 6), ((64, 8), (2, 0), 4), ((1000, 4), (0, 1), 10)])
+def test_captured_even_step_counts_replay(shape, bc, steps):
+    """A call of an even number of steps leaves the two buffers as it found
+    them, whatever the steps per launch: its graph advances the state at every
+    replay, bit for bit as the calls themselves do."""
+    import torch
+    from paper_2510_14712_amd import lbm
+    lbm.load()
+    kw = dict(KW, walls=WALLS) if bc[0] == 2 else KW
+    rho, u, T = inputs.random_state(2, shape, 59, RHOC, 1.1 * TC, drho=0.04, du=0.06, dT=0.03)
+    print(f"case {shape} bc={bc} steps {steps}", flush=True)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with lbm.Lattice(2, shape, bc=bc + (0,), storage="f64", stream=s, **kw) as a, \
+            lbm.Lattice(2, shape, bc=bc + (0,), storage="f64", stream=s, **kw) as b, torch.cuda.stream(s):
+        a.init(rho, u, T).step(2)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            a.step(steps)
+        b.init(rho, u, T).step(2)
+        for _ in range(3):
+            graph.replay()
+            b.step(steps)
+            torch.cuda.synchronize()
+            for p, q in zip(a.get_populations(), b.get_populations()):
+                assert torch.equal(p, q)

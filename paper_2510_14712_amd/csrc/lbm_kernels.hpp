@@ -266,8 +266,9 @@ __global__ void __launch_bounds__(BX) k_fields(Grid g, Phys<C> ph, MomSrc<C> m, 
 // partials; no field array is written but, with Peng-Robinson, T (the next
 // warm start).  Bound by HBM: 24 bytes read (FP32) and 48 written per cell
 // (256^3 cells: 0.28 ms, the sums 0.14 ms; through the field arrays the fields
-// pass took 0.23 ms and each of the two that read them 0.20 to 0.23).  A block takes a contiguous run of 256-cell units, neighbouring runs on one XCD,
-// whose L2 then holds the Laplacian rows that they share.
+// pass took 0.23 ms and each of the two that read them 0.20 to 0.23).  A block
+// takes a contiguous run of 256-cell units, neighbouring runs on one XCD, whose
+// L2 then holds the Laplacian rows that they share.
 constexpr int RED_VALS = 7;  // rho, j_x, j_y, j_z, G, non-finite count, inadmissible count
 constexpr int READ_BLOCKS = 2048;  // 8 blocks of 256 threads per compute unit
 

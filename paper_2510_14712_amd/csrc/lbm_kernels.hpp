@@ -581,6 +581,10 @@ __global__ void __launch_bounds__(BX) k_collide(Grid g, Phys<typename S::C> ph, 
     constexpr int Q = Lattice<D>::Q;
     int x, y, z;
     if (!flat_cell(g, x, y, z)) return;
+    // The last planes first: k_moments and the field passes have just left them
+    // in the caches, and the next k_moments begins where this pass ends (128^3,
+    // Peng-Robinson, FP32: ten steps and a snapshot 4.34 -> 4.26 ms).
+    z = g.nz - 1 - z;
     const long long N = g.N;
     long long c = cell_index<D>(g, x, y, z);
     C rho = fl.rho[c], P = fl.P[c], T = fl.T[c];

@@ -603,22 +603,27 @@ template <int D, class S> struct Impl {
     }
     static int block2d_step(lbm_ctx *c, int n) {
         const long long every = c->p.check_every;
-        // As many launches, or one more, as turn the two buffers like n single
-        // steps would: a captured call of an even number of steps ends in the
-        // buffer it began in and can be replayed, as on the other paths.
-        int launches = (n + c->b2_steps - 1) / c->b2_steps;
-        if ((launches ^ n) & 1) launches++;
-        for (; n > 0; launches--) {
-            int k = every > 0 ? std::min(n, c->b2_steps) : (n + launches - 1) / launches;
-            if (every > 0) k = (int)std::min<long long>(k, every - c->steps_done % every);
-            block2d_launch(c, k);
-            int rc = last_launch();
-            if (rc) return rc;
-            n -= k;
-            c->steps_done += k;
+        while (n > 0) {
+            // the steps up to the next check
+            int m = every > 0 ? (int)std::min<long long>(n, every - c->steps_done % every) : n;
+            n -= m;
+            // As many launches, or one more, as turn the two buffers like m
+            // single steps would: a captured call of an even number of steps
+            // ends in the buffer it began in and can be replayed, as on the
+            // other paths.
+            int launches = (m + c->b2_steps - 1) / c->b2_steps;
+            if ((launches ^ m) & 1) launches++;
+            for (; m > 0; launches--) {
+                const int k = (m + launches - 1) / launches;
+                block2d_launch(c, k);
+                const int rc = last_launch();
+                if (rc) return rc;
+                m -= k;
+                c->steps_done += k;
+            }
             if (every > 0 && c->steps_done % every == 0) {
                 double tmp[RED_VALS];
-                rc = conservation(c, tmp);
+                const int rc = conservation(c, tmp);
                 if (rc) return rc;
             }
         }

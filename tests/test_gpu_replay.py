@@ -1,0 +1,69 @@
+"""A call of an even number of steps ends in the buffer it began in, whatever the
+path and the steps per launch: captured into a graph, it advances the state at
+every replay, bit for bit as the calls themselves do.
+
+Small D2Q9 lattices (several steps per launch) with a check interval beyond the
+steps taken; and checks inside a call, which change nothing.
+"""
+import pytest
+
+from paper_2510_14712_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+ST = inputs.states()
+KW = inputs.physics(ST)
+RHOC, TC = ST["critical"]["rho"], ST["critical"]["T"]
+
+
+def walls(D):
+    return (((0.0, -0.04, 0.02)[:D], 0.95 * TC), ((0.0, 0.08, -0.03)[:D], 1.25 * TC))
+
+
+def same(a, b):
+    import torch
+    torch.cuda.synchronize()
+    for p, q in zip(a.get_populations(), b.get_populations()):
+        assert torch.equal(p, q)
+    ma, mb = a.moments(), b.moments()
+    for k in ma:
+        assert torch.equal(ma[k], mb[k]), k
+
+
+@pytest.mark.parametrize("shape,bc,steps,every", [((64, 4), (0, 0), 6, 100), ((64, 8), (2, 0), 4, 100),
+                                                  ((1000, 4), (0, 1), 10, 13)])
+def test_captured_steps_with_a_check_interval_replay(shape, bc, steps, every):
+    import torch
+    from paper_2510_14712_amd import lbm
+    lbm.load()
+    kw = dict(KW, walls=walls(2)) if bc[0] == 2 else KW
+    rho, u, T = inputs.random_state(2, shape, 59, RHOC, 1.1 * TC, drho=0.04, du=0.06, dT=0.03)
+    print(f"case {shape} bc={bc} steps {steps} check_every {every}", flush=True)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with lbm.Lattice(2, shape, bc=bc + (0,), storage="f64", stream=s, check_every=every, **kw) as a, \
+            lbm.Lattice(2, shape, bc=bc + (0,), storage="f64", stream=s, **kw) as b, torch.cuda.stream(s):
+        a.init(rho, u, T).step(2)
+        b.init(rho, u, T).step(2)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            a.step(steps)  # no check due: 2 + steps < every
+        for _ in range(3):
+            graph.replay()
+            b.step(steps)
+            same(a, b)
+
+
+@pytest.mark.parametrize("shape,bc", [((64, 4), (0, 0)), ((300, 9), (1, 1)), ((203, 5), (2, 0))])
+def test_checks_between_the_launches_change_nothing(shape, bc):
+    from paper_2510_14712_amd import lbm
+    lbm.load()
+    kw = dict(KW, walls=walls(2)) if bc[0] == 2 else KW
+    rho, u, T = inputs.random_state(2, shape, 60, RHOC, 1.1 * TC, drho=0.04, du=0.06, dT=0.03)
+    print(f"case {shape} bc={bc}", flush=True)
+    with lbm.Lattice(2, shape, bc=bc + (0,), storage="f32", check_every=5, **kw) as a, \
+            lbm.Lattice(2, shape, bc=bc + (0,), storage="f32", **kw) as b:
+        a.init(rho, u, T).step(3).step(19)
+        b.init(rho, u, T).step(22)
+        same(a, b)

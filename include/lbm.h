@@ -176,6 +176,12 @@ int lbm_init(lbm_ctx *ctx, const double *dev_rho, const double *dev_u, const dou
  * every check_every-th step (a blocking fields pass and reduction); the first
  * failing check ends the call with LBM_ENAN or LBM_EUNSTABLE, the steps
  * before it having been taken.
+ * A call inside which no check falls due can be captured into a HIP graph.
+ * With an even n the call ends in the buffer it began in and every replay
+ * advances the state by n steps.  On the single-pass path (lbm_is_fused) a
+ * step must have been taken since lbm_init or lbm_set_populations both when
+ * the call is captured and when it is replayed (the graph holds the form of
+ * its input set, which those two leave in another one).
  * Errors: LBM_ESTATE (not initialised), LBM_EINVAL (n < 0), LBM_ENAN,
  * LBM_EUNSTABLE, LBM_EDEVICE. */
 int lbm_step(lbm_ctx *ctx, int n);

@@ -63,9 +63,10 @@ __global__ void __launch_bounds__(64 * RED_VALS) k_reduce_final(int nblocks, con
 // 0.96).
 template <int D, class S>
 __global__ void __launch_bounds__(BX) k_get_pops(Grid g, RefPops ref, const typename S::T *__restrict__ fi,
-                                                 double *__restrict__ fo, double *__restrict__ go, int pull) {
+                                                 double *__restrict__ fo, double *__restrict__ go, SetForm form) {
     using C = typename S::C;
     constexpr int Q = Lattice<D>::Q;
+    const int pull = form.pull();
     int x, y, z;
     if (!flat_cell(g, x, y, z)) return;
     long long c = cell_index<D>(g, x, y, z);
@@ -78,11 +79,13 @@ __global__ void __launch_bounds__(BX) k_get_pops(Grid g, RefPops ref, const type
 }
 template <int D, class S>
 __global__ void __launch_bounds__(BX) k_set_pops(Grid g, RefPops ref, const double *__restrict__ fi,
-                                                 const double *__restrict__ gi, typename S::T *__restrict__ fo) {
+                                                 const double *__restrict__ gi, typename S::T *__restrict__ fo,
+                                                 int *form) {
     using C = typename S::C;
     constexpr int Q = Lattice<D>::Q;
     int x, y, z;
     if (!flat_cell(g, x, y, z)) return;
+    mark_form(form, 0);
     long long c = cell_index<D>(g, x, y, z);
     const long long xy = x + (long long)g.nx * y;
 #pragma unroll
@@ -410,11 +413,15 @@ template <int D, class S> struct Impl {
         int rc0 = check_inputs(c, rho, u, Tf);
         if (rc0) return rc0;
         hipLaunchKernelGGL((k_init<D, S>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, make_phys<double>(c->p),
-                           c->ref, rho, u, Tf, (T *)c->f[c->cur]);
+                           c->ref, rho, u, Tf, (T *)c->f[c->cur], form_flag(c, c->cur));
         c->pulled = 0;
         int rc = last_launch();
         return rc ? rc : fused_prepare(c);
     }
+    // the form flag of buffer b (null where the host's flag holds), the form of
+    // the current set
+    static int *form_flag(const lbm_ctx *c, int b) { return c->form ? (int *)c->form + 16 * b : nullptr; }
+    static SetForm set_form(const lbm_ctx *c) { return SetForm{c->pulled, form_flag(c, c->cur)}; }
     static MomSrc<C> field_moments(lbm_ctx *c) {
         return MomSrc<C>{get_fields<C>(c).rho, (long long)c->p.nx * c->p.ny, (long long)c->grid.N, D + 1};
     }
@@ -427,7 +434,7 @@ template <int D, class S> struct Impl {
     }
     static void moments_launch(lbm_ctx *c) {
         hipLaunchKernelGGL((k_moments<D, S>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, c->ref,
-                           (const T *)c->f[c->cur], get_fields<C>(c), c->pulled);
+                           (const T *)c->f[c->cur], get_fields<C>(c), set_form(c));
     }
     static void lap_launch(lbm_ctx *c, const MomSrc<C> &m) {
         hipLaunchKernelGGL((k_lap<D, C>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, m, get_fields<C>(c).lap);
@@ -522,12 +529,11 @@ template <int D, class S> struct Impl {
         if (c->grid.wallx)
             hipLaunchKernelGGL((k_collide<D, S, true>), flat_grid(c), dim3(BX), 0, c->stream, c->grid,
                                make_phys<C>(c->p), c->ref, (const T *)c->f[c->cur], fl, (T *)c->f[nxt], fS, fs, w,
-                               (C *)c->ghost, c->pulled);
+                               (C *)c->ghost, set_form(c), form_flag(c, nxt));
         else
             hipLaunchKernelGGL((k_collide<D, S, false>), flat_grid(c), dim3(BX), 0, c->stream, c->grid,
                                make_phys<C>(c->p), c->ref, (const T *)c->f[c->cur], fl, (T *)c->f[nxt], fS, fs, w,
-                               (C *)c->ghost, c->pulled);
-        c->pulled = c->grid.wallx ? 0 : 1;
+                               (C *)c->ghost, set_form(c), form_flag(c, nxt));
         if (c->grid.wallx)
             hipLaunchKernelGGL((k_wall_emit<D, S>), dim3((unsigned)((c->p.ny + 63) / 64), (unsigned)c->p.nz, 2u),
                                dim3(64), 0, c->stream, c->grid, make_phys<C>(c->p), c->ref, w, fl,
@@ -740,12 +746,12 @@ template <int D, class S> struct Impl {
     }
     static int get_pops(lbm_ctx *c, double *f, double *g) {
         hipLaunchKernelGGL((k_get_pops<D, S>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, c->ref,
-                           (const T *)c->f[c->cur], f, g, c->pulled);
+                           (const T *)c->f[c->cur], f, g, set_form(c));
         return last_launch();
     }
     static int set_pops(lbm_ctx *c, const double *f, const double *g) {
         hipLaunchKernelGGL((k_set_pops<D, S>), flat_grid(c), dim3(BX), 0, c->stream, c->grid, c->ref, f, g,
-                           (T *)c->f[c->cur]);
+                           (T *)c->f[c->cur], form_flag(c, c->cur));
         c->pulled = 0;
         int rc = last_launch();
         return rc ? rc : fused_prepare(c);
@@ -1034,7 +1040,8 @@ int lbm_create(const lbm_params *params, lbm_ctx **out) {
     // the population sets (one buffer per ping-pong slot holds both sets, f_i
     // and g_i side by side; the g pointer is the f buffer offset by one
     // element), the field arrays, the wall ghosts, and the fused step's side
-    // channel, inbound slots, surrogate temperatures and their acceptance bits.
+    // channel, inbound slots, surrogate temperatures and their acceptance bits;
+    // the form flags of the multi-kernel step (with x walls every set is arrived).
     struct Part {
         void **dst;
         size_t bytes;
@@ -1044,6 +1051,7 @@ int lbm_create(const lbm_params *params, lbm_ctx **out) {
                           {&c->f[1], 2 * pop_bytes},
                           {&c->work, field_bytes},
                           {&c->ghost, c->grid.wallx ? (size_t)2 * params->ny * params->nz * c->Q * cb : 0},
+                          {&c->form, !c->fused && !c->grid.wallx ? 2 * 16 * sizeof(int) : 0},
                           {&c->Mc[0], c->fused ? c->mc_bytes : 0},
                           {&c->Mc[1], c->fused ? c->mc_bytes : 0},
                           {&c->IN[0], c->fused ? c->in_bytes : 0},

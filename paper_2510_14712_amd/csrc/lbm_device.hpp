@@ -190,12 +190,12 @@ template <class T> __device__ __forceinline__ void store_pair(T *p, long long j,
 
 // Stored population sets come in two forms.  After initialisation (and after
 // lbm_set_populations) the set holds the arrived populations f_i(x) that the
-// next collision uses in place.  The fused step stores the post-collision set
-// instead and streams on the way in: the population arriving at x with
-// velocity c_i is read from x - c_i (wrapped on a periodic axis, clamped to
-// the edge cell on a zero-gradient axis, which is the streaming rule of
-// Sec. 3.2 with the boundary reading of the oracle).  `pull` selects the
-// form: 0 reads x itself, 1 reads x - c.
+// next collision uses in place.  A step stores the post-collision set instead
+// and streams on the way in: the population arriving at x with velocity c_i is
+// read from x - c_i (wrapped on a periodic axis, clamped to the edge cell on a
+// zero-gradient axis, which is the streaming rule of Sec. 3.2 with the boundary
+// reading of the oracle).  `pull` selects the form: 0 reads x itself, 1 reads
+// x - c.
 __host__ __device__ __forceinline__ int pull_coord(int x, int c, int n, int clamp, int pull) {
     const int p = x - pull * c;
     if (clamp) return p < 0 ? 0 : (p >= n ? n - 1 : p);
@@ -210,6 +210,20 @@ __host__ __device__ __forceinline__ long long arrived_index(const Grid &g, int i
     const int sy = pull_coord(y, cy_of(i), g.ny, g.clampy, pull);
     const int sz = D == 3 ? pull_coord(z, cz_of(i), g.nz, g.clampz, pull) : 0;
     return pop_index<Q>(g, i, sz, sx + (long long)g.nx * sy);
+}
+
+// Form of a stored set: the host's flag, or (dev not null: the multi-kernel step)
+// a flag in device memory beside each buffer, which whoever writes the buffer
+// sets.  A flag of the host's would be fixed in a captured graph: a step
+// captured straight after lbm_init would read its own output as an arrived set
+// at the next replay.
+struct SetForm {
+    int host;
+    const int *dev;
+    __device__ __forceinline__ int pull() const { return dev ? __builtin_amdgcn_readfirstlane(*dev) : host; }
+};
+__device__ __forceinline__ void mark_form(int *form, int pull) {
+    if (form && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0) *form = pull;
 }
 
 // ---------------------------------------------------------------------------

@@ -17,6 +17,7 @@ struct lbm_ctx {
     void *g[2] = {nullptr, nullptr};  // f[k] + one element (not separately allocated)
     int cur = 0;                      // index of the buffer holding the state
     int pulled = 0;                   // 1: the state is the post-collision set (read from x - c_i)
+    void *form = nullptr;             // multi-kernel step: that flag of each buffer, on the device, 64 bytes apart
     void *work = nullptr;             // per-cell field arrays
     lbm::RefPops ref;
     hipStream_t stream = nullptr;

@@ -89,11 +89,12 @@ template <class C> __device__ __forceinline__ AxisEq<C> axis_eq(C u, C theta) {
 template <int D, class S>
 __global__ void __launch_bounds__(BX) k_init(Grid g, Phys<double> ph, RefPops ref, const double *__restrict__ rho,
                                              const double *__restrict__ u, const double *__restrict__ T,
-                                             typename S::T *__restrict__ fo) {
+                                             typename S::T *__restrict__ fo, int *form) {
     using C = typename S::C;
     constexpr int Q = Lattice<D>::Q;
     int x, y, z;
     if (!flat_cell(g, x, y, z)) return;
+    mark_form(form, 0);
     long long c = cell_index<D>(g, x, y, z);
     double r = rho[c], t = T[c];
     double P, e;
@@ -132,9 +133,10 @@ __global__ void __launch_bounds__(BX) k_init(Grid g, Phys<double> ph, RefPops re
 // Bound by HBM: Q pairs read per cell, one access each.
 template <int D, class S>
 __global__ void __launch_bounds__(BX) k_moments(Grid g, RefPops ref, const typename S::T *__restrict__ fi,
-                                                Fields<typename S::C> fl, int pull) {
+                                                Fields<typename S::C> fl, SetForm form) {
     using C = typename S::C;
     constexpr int Q = Lattice<D>::Q;
+    const int pull = form.pull();
     int x, y, z;
     if (!flat_cell(g, x, y, z)) return;
     long long c = cell_index<D>(g, x, y, z);
@@ -562,8 +564,9 @@ __global__ void __launch_bounds__(64) k_wall_emit(Grid g, Phys<typename S::C> ph
 // ---------------------------------------------------------------------------
 // fS, fs: filtered |grad^4 S| and |grad^4 |grad s|| of the shock-capturing
 // passes, or null without shock capturing.  The arrived populations are read
-// as (f, g) pairs in the form `pull` says and the post-collision pairs stored
-// at the cell itself (aligned rows; the next step streams them on the way in).
+// as (f, g) pairs in the form `form` says and the post-collision pairs stored
+// at the cell itself (aligned rows; the next step streams them on the way in;
+// form_out: the output buffer's flag).
 // With x walls (WALL; w: wall states, gb: ghost buffer) the set is pushed to
 // x + c_i instead, since what a wall ghost emits has no place of its own in the
 // post-collision set.  Bound by HBM: 2 Q pairs and about 30 field values per
@@ -576,11 +579,13 @@ __global__ void __launch_bounds__(BX) k_collide(Grid g, Phys<typename S::C> ph, 
                                                 typename S::T *__restrict__ fo,
                                                 const typename S::C *__restrict__ fS,
                                                 const typename S::C *__restrict__ fs, Walls w,
-                                                typename S::C *__restrict__ gb, int pull) {
+                                                typename S::C *__restrict__ gb, SetForm form, int *form_out) {
     using C = typename S::C;
     constexpr int Q = Lattice<D>::Q;
+    const int pull = form.pull();
     int x, y, z;
     if (!flat_cell(g, x, y, z)) return;
+    mark_form(form_out, 1);
     // The last planes first: k_moments and the field passes have just left them
     // in the caches, and the next k_moments begins where this pass ends (128^3,
     // Peng-Robinson, FP32: ten steps and a snapshot 4.34 -> 4.26 ms).

@@ -2,8 +2,12 @@
 path and the steps per launch: captured into a graph, it advances the state at
 every replay, bit for bit as the calls themselves do.
 
-Small D2Q9 lattices (several steps per launch) with a check interval beyond the
-steps taken; and checks inside a call, which change nothing.
+* Small D2Q9 lattices (several steps per launch) with a check interval beyond the
+  steps taken, and checks inside a call, which change nothing.
+* The multi-kernel step and the walled ones: captured straight after lbm_init,
+  where the set is in the arrived form that only the first step meets, and
+  replayed again after lbm_set_populations.  Capturing runs nothing: a read-back
+  before the first replay still finds the initial state.
 """
 import pytest
 
@@ -14,6 +18,9 @@ pytestmark = pytest.mark.gpu
 ST = inputs.states()
 KW = inputs.physics(ST)
 RHOC, TC = ST["critical"]["rho"], ST["critical"]["T"]
+PRC = ST["peng_robinson"]
+PR_KW = dict(a=PRC["a"], b=PRC["b"], R=PRC["R"], cv=PRC["c0"], mu=0.05, eta=0.05, k=0.05 * (PRC["c0"] + PRC["R"]),
+             kappa=0.01, eos="pr", pr=dict(m=PRC["m"], Tc=PRC["Tc"], c0=PRC["c0"], c1=PRC["c1"]))
 
 
 def walls(D):
@@ -66,4 +73,54 @@ def test_checks_between_the_launches_change_nothing(shape, bc):
             lbm.Lattice(2, shape, bc=bc + (0,), storage="f32", **kw) as b:
         a.init(rho, u, T).step(3).step(19)
         b.init(rho, u, T).step(22)
+        same(a, b)
+
+
+MULTI = [
+    ("f32", 3, (33, 9, 6), (0, 0, 0), "pr"), ("f64", 2, (90, 17), (0, 1, 0), "pr"),
+    ("f32", 3, (20, 9, 9), (1, 0, 0), "sc"), ("bf16", 3, (24, 8, 7), (0, 0, 1), "open z"),
+    ("f32", 3, (15, 6, 5), (2, 0, 0), "walls"), ("f32", 2, (64, 4), (2, 0, 0), "walls"),
+]
+
+
+@pytest.mark.parametrize("storage,D,shape,bc,kind", MULTI)
+def test_steps_captured_straight_after_init_replay(storage, D, shape, bc, kind):
+    import torch
+    from paper_2510_14712_amd import lbm
+    lbm.load()
+    kw, rho0, T0 = KW, RHOC, 1.1 * TC
+    if kind == "pr":
+        kw, rho0, T0 = PR_KW, PRC["rho_c"], 1.1 * PRC["Tc"]
+    elif kind == "sc":
+        kw = dict(KW, sc=(0.05, 0.05, 0.05))
+    elif kind == "walls":
+        kw = dict(KW, walls=walls(D))
+    rho, u, T = inputs.random_state(D, shape, 61, rho0, T0, drho=0.04, du=0.06, dT=0.03)
+    print(f"case {kind} {storage} D={D} {shape} bc={bc}", flush=True)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    kw = dict(kw, bc=bc, storage=storage, stream=s, ref_rho=rho0, ref_T=T0)
+    with lbm.Lattice(D, shape, **kw) as a, lbm.Lattice(D, shape, **kw) as b, torch.cuda.stream(s):
+        assert not a.fused
+        a.init(rho, u, T)
+        b.init(rho, u, T)
+        start = b.get_populations()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            a.step(2)
+        same(a, b)
+        for _ in range(3):
+            graph.replay()
+            b.step(2)
+            same(a, b)
+        for lat in (a, b):
+            lat.set_populations(*start)
+        for _ in range(2):
+            graph.replay()
+            b.step(2)
+            same(a, b)
+        # and on without the graph
+        a.step(3)
+        b.step(3)
         same(a, b)

@@ -53,7 +53,7 @@ struct EosPoint {
     double P, e, cv, cs2, dPdT;
 };
 // L(rho), the logarithm of the energy departure: once per cell
-template <class C> __device__ __forceinline__ double pr_log(const Phys<C> &ph, double rho) {
+template <class C> __host__ __device__ __forceinline__ double pr_log(const Phys<C> &ph, double rho) {
     const double b = (double)ph.b, r2 = 1.4142135623730951;
     return log((1.0 + (1.0 + r2) * b * rho) / (1.0 + (1.0 - r2) * b * rho)) / (2.0 * r2 * b);
 }
@@ -81,18 +81,20 @@ template <class C> __device__ __forceinline__ EosPoint pr_eos(const Phys<C> &ph,
 }
 // Newton's method on e(rho, T) = e from T0 (a non-positive or non-finite
 // start is replaced by the dilute estimate e / c0, else T_c), a step that
-// would leave T > 0 halved; converged when the step is below 1e-15 T.
-// `iters` receives the iterations taken (50 at most).
+// would leave T > 0 halved; converged when the step is below 1e-15 T.  A step
+// that is not finite (an infinite or NaN energy, a density outside the equation
+// of state's range) has no half that would end the halving: T is then not finite
+// and the solve ends.  `iters` receives the iterations taken (50 at most).
 //
 // With s = sqrt(T / T_c) the energy is c0 T + c1 T^2 / 2 - K (1 + m - m s),
 // K = a (1 + m) L, and c_v = c0 + c1 T + K m / (2 T_c s): one square root and
 // one division per iteration, where the closed forms of pr_eos take two and
 // three (fields pass, 128^3 cells, FP32, five iterations a cell: 143 -> 68 us).
 template <class C>
-__device__ __forceinline__ double pr_temperature(const Phys<C> &ph, double rho, double e, double T0, double L,
-                                                 int &iters) {
+__host__ __device__ __forceinline__ double pr_temperature(const Phys<C> &ph, double rho, double e, double T0, double L,
+                                                          int &iters) {
     double t = T0;
-    if (!(t > 1e-3 * ph.pr_Tc)) t = e / ph.pr_c0;
+    if (!(t > 1e-3 * ph.pr_Tc && __builtin_isfinite(t))) t = e / ph.pr_c0;
     if (!(t > 1e-3 * ph.pr_Tc)) t = ph.pr_Tc;
     const double m = ph.pr_m, inv_Tc = 1.0 / ph.pr_Tc, K = (double)ph.a * (1.0 + m) * L;
     const double e0 = e + K * (1.0 + m), Km = K * m, hk = 0.5 * Km * inv_Tc;
@@ -102,9 +104,13 @@ __device__ __forceinline__ double pr_temperature(const Phys<C> &ph, double rho, 
         const double f = t * (ph.pr_c0 + 0.5 * ph.pr_c1 * t) + Km * s - e0;  // e(rho, t) - e
         double dt = f * s / ((ph.pr_c0 + ph.pr_c1 * t) * s + hk);
         double tn = t - dt;
-        while (!(tn > 0.0) && fabs(dt) > 1e-300) {
-            dt *= 0.5;
-            tn = t - dt;
+        if (!(tn > 0.0)) {
+            if (!__builtin_isfinite(dt)) tn = __builtin_nan("");
+            else
+                while (!(tn > 0.0) && fabs(dt) > 1e-300) {
+                    dt *= 0.5;
+                    tn = t - dt;
+                }
         }
         t = tn;
         iters = it;

@@ -1,0 +1,76 @@
+"""The Peng-Robinson Newton solve of the kernels, compiled for the host: it ends
+for every input -- infinities, NaN, densities outside the equation of state's
+range -- in a temperature, or in a value that is not finite where the energy is
+not, and returns the oracle's temperature where there is one."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2510_14712_amd import build, inputs
+
+ST = inputs.states()
+PRC = ST["peng_robinson"]
+PR = dict(m=PRC["m"], Tc=PRC["Tc"], c0=PRC["c0"], c1=PRC["c1"])
+
+MAIN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "lbm_device.hpp"
+int main(int argc, char **argv) {
+    lbm::Phys<double> ph = {};
+    double *k[] = {&ph.a, &ph.b, &ph.R, &ph.pr_m, &ph.pr_Tc, &ph.pr_c0, &ph.pr_c1};
+    for (int i = 0; i < 7; i++) *k[i] = strtod(argv[1 + i], nullptr);
+    for (int i = 8; i + 2 < argc; i += 3) {
+        const double rho = strtod(argv[i], nullptr), e = strtod(argv[i + 1], nullptr), T0 = strtod(argv[i + 2], nullptr);
+        int it = -1;
+        const double t = lbm::pr_temperature(ph, rho, e, T0, lbm::pr_log(ph, rho), it);
+        printf("%.17g %d\n", t, it);
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def newton(tmp_path_factory):
+    d = tmp_path_factory.mktemp("newton")
+    src, exe = d / "newton.hip", d / "newton"
+    src.write_text(MAIN)
+    subprocess.run([build.HIPCC, "--offload-host-only", "-O2", "-std=c++17", "-I", build.CSRC, str(src), "-o", str(exe)],
+                   check=True, capture_output=True)
+    consts = [repr(float(PRC[k])) for k in ("a", "b", "R", "m", "Tc", "c0", "c1")]
+
+    def run(cases):
+        # a solve that does not end is stopped here
+        out = subprocess.run([str(exe), *consts, *[repr(float(v)) for c in cases for v in c]], check=True,
+                             capture_output=True, text=True, timeout=20).stdout.split()
+        return np.array(out[0::2], float), np.array(out[1::2], int)
+
+    return run
+
+
+@pytest.mark.parametrize("T0", [0.0, 0.9 * PRC["Tc"], np.inf, np.nan])
+@pytest.mark.parametrize("rho", [PRC["rho_c"], 0.0, -1.0, -1e3, 3.0 / PRC["b"], np.inf, np.nan])
+def test_solve_ends_where_the_energy_is_not_finite(newton, rho, T0):
+    T, iters = newton([(rho, e, T0) for e in (-np.inf, np.inf, np.nan)])
+    assert not np.isfinite(T).any() and (iters <= 50).all()
+
+
+@pytest.mark.parametrize("rho", [0.0, -1.0, 3.0 / PRC["b"], 1e-300, 1e300])
+def test_solve_ends_for_any_finite_energy(newton, rho):
+    _, iters = newton([(rho, e, T0) for e in (-1e308, -1.0, 0.0, 1e-320, 1.0, 1e308) for T0 in (0.0, 0.2, 1e300)])
+    assert (iters <= 50).all()
+
+
+def test_temperatures_are_those_the_energies_came_from(newton):
+    rng = np.random.default_rng(5)
+    rho, T = PRC["rho_c"] * rng.uniform(0.05, 2.5, 200), PRC["Tc"] * rng.uniform(0.7, 1.6, 200)
+    p = oracle.Params(3, (1, 1, 1), a=PRC["a"], b=PRC["b"], R=PRC["R"], pr=PR)
+    e = np.array([oracle.eos(p, float(r), float(t))["e"] for r, t in zip(rho, T)])
+    for T0 in (0.0, PRC["Tc"]):
+        got, iters = newton(list(zip(rho, e, np.full(200, T0))))
+        # the energy's rounding, eps (|e| + a (1 + m)^2 L), over c_v: a few eps of T
+        assert np.max(np.abs(got / T - 1.0)) <= 1e-13
+        assert iters.max() <= 12

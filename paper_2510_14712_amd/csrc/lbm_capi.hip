@@ -344,18 +344,20 @@ template <int D, class S> struct Impl {
         const int nxt = 1 - c->mcc;
         const int rows0 = fold(c) || kfold(c) ? 0 : c->p.nz, ends = D == 3 ? 2 * c->nseg : 0;
         const long long per = (long long)c->ntx * c->nty * TL::PMAX, plane = (long long)c->p.nx * c->p.ny;
-        // rows of the perimeter cells, then of the segment ends
-        auto launch = [&](int rows, int erows) {
+        // rows of the perimeter cells, then segment ends [e0, e0 + erows)
+        auto launch = [&](int rows, int e0, int erows) {
+            if (rows + erows == 0) return;
             const long long n = std::max(rows ? per : 0, erows ? plane : 0);
             hipLaunchKernelGGL((k_fused_fixup<D, TL, C>), dim3((unsigned)((n + BX - 1) / BX), (unsigned)(rows + erows)),
-                               dim3(BX), 0, c->stream, c->grid, c->ntx, c->nty, c->nseg, rows, (C *)c->Mc[nxt],
+                               dim3(BX), 0, c->stream, c->grid, c->ntx, c->nty, c->nseg, rows, e0, (C *)c->Mc[nxt],
                                (const C *)c->IN[nxt]);
         };
-        if (rows0 + ends > 65535) {  // beyond a grid's second extent (lattices of more than about 60000 planes)
-            launch(rows0, 0);
-            launch(0, ends);
-        } else if (rows0 + ends > 0) {
-            launch(rows0, ends);
+        constexpr int MAX_ROWS = 65535;  // of a grid's second extent
+        if (rows0 + ends <= MAX_ROWS) {
+            launch(rows0, 0, ends);
+        } else {  // tall lattices of many segments
+            launch(rows0, 0, 0);
+            for (int e0 = 0; e0 < ends; e0 += MAX_ROWS) launch(0, e0, std::min(MAX_ROWS, ends - e0));
         }
         if (fold(c)) return;
         c->mcc = nxt;

@@ -1512,13 +1512,13 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
 // layers).  Block rows y < nrows0: the perimeter cells of the tiles in plane y,
 // unless it is a segment end (nrows0 = nz, or 0 where the next step completes
 // them); rows from nrows0 on (D = 3): every cell of the first and last plane of
-// each segment.  One launch for both: on small lattices a second one cost as
-// much as the work.
+// each segment, from end end0 on (two a segment).  One launch for both: on small
+// lattices a second one cost as much as the work.
 //
 // A thread's loads are issued together before its sums, one memory round trip
 // instead of one per moment.
 template <int D, class TL, class C>
-__global__ void __launch_bounds__(BX) k_fused_fixup(Grid g, int ntx, int nty, int nseg, int nrows0,
+__global__ void __launch_bounds__(BX) k_fused_fixup(Grid g, int ntx, int nty, int nseg, int nrows0, int end0,
                                                     C *__restrict__ Mc, const C *__restrict__ IN) {
     // 32-bit index arithmetic throughout (tiles x perimeter slots, planes and
     // layers all fit); the z plane and its segment are uniform per block
@@ -1553,7 +1553,7 @@ __global__ void __launch_bounds__(BX) k_fused_fixup(Grid g, int ntx, int nty, in
         gxv = tx * TL::TX + lx;
         gyv = ty * TL::TY + ly;
     } else {
-        const int e = (int)blockIdx.y - nrows0;
+        const int e = (int)blockIdx.y - nrows0 + end0;
         s = e >> 1;
         zlo = seg_lo(s, nz, nseg);
         zhi = seg_lo(s + 1, nz, nseg) - 1;

@@ -134,6 +134,14 @@ template <class C> __device__ __forceinline__ C vdw_cs2(const Phys<C> &p, C rho,
 // division, well inside the FP32 form's error against the FP64 method
 template <class C> __device__ __forceinline__ C fdiv(C a, C b) { return a / b; }
 template <> __device__ __forceinline__ float fdiv<float>(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
+// 1 / v by fdiv, or (CORRECTED) in FP32 with one Newton correction of the
+// hardware reciprocal, which rounds like the division but for a last bit now and
+// then at two instructions instead of ten
+template <bool CORRECTED, class C> __device__ __forceinline__ C reciprocal(C v) { return fdiv(C(1), v); }
+template <> __device__ __forceinline__ float reciprocal<true, float>(float v) {
+    const float r = __builtin_amdgcn_rcpf(v);
+    return __builtin_fmaf(__builtin_fmaf(-v, r, 1.0f), r, r);
+}
 // pressure and adiabatic sound speed squared together (eqs. Pvdw,
 // vdW_speed_of_sound); FP32 shares one reciprocal of 1 - b rho, FP64 takes the
 // two closed forms as written

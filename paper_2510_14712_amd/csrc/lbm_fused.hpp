@@ -205,12 +205,13 @@ template <class C> struct CollideIn {
 };
 
 // Relax f, g in place to the post-collision populations (eqs. fLBGK, gLBGK
-// with the attractors of eqs. LBMeq, LBMstar, LBMeqG, LBMgstar).
-template <int D, class C>
+// with the attractors of eqs. LBMeq, LBMstar, LBMeqG, LBMgstar).  RHO_C: 1/rho
+// corrected.
+template <int D, bool RHO_C = false, class C>
 __device__ __forceinline__ void collide_cell(const Phys<C> &ph, const CollideIn<C> &in, C *f, C *g) {
     constexpr int Q = Lattice<D>::Q;
     const C rho = in.rho, P = in.P;
-    const C inv_rho = fdiv(C(1), rho);
+    const C inv_rho = reciprocal<RHO_C>(rho);
     const C theta = P * inv_rho;
     C qc[3], Phi[3], FF = 0;
     for (int d = 0; d < D; d++) {

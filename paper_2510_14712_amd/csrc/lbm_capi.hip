@@ -290,7 +290,6 @@ template <int D, class S> struct Impl {
         a.nty = c->nty;
         a.nseg = c->nseg;
         a.nsub = c->nsub;
-        a.fold = kfold(c) ? 1 : 0;
         a.nlay = c->nlay;
         a.chunk = c->chunk;
         a.pull = c->pulled;
@@ -314,14 +313,15 @@ template <int D, class S> struct Impl {
         a.accw = 2 * ((c->p.nx + 63) / 64);
         a.inv_cv_d = 1.0 / (double)(float)c->p.cv;
         const dim3 grid((unsigned)(c->ntx * c->nty * c->nseg * c->nsub));
-        const bool fast = fast_instance<M>(c);
-        if constexpr (M && std::is_same<C, float>::value) {
-            if (fast) hipLaunchKernelGGL((k_fused<D, S, TL, true, true>), grid, dim3(TL::NT), 0, c->stream, a);
-            else hipLaunchKernelGGL((k_fused<D, S, TL, true, false>), grid, dim3(TL::NT), 0, c->stream, a);
-        } else {
-            if (fast) hipLaunchKernelGGL((k_fused<D, S, TL, false, true>), grid, dim3(TL::NT), 0, c->stream, a);
-            else hipLaunchKernelGGL((k_fused<D, S, TL, false, false>), grid, dim3(TL::NT), 0, c->stream, a);
-        }
+        auto launch = [&](auto FAST, auto FOLD) {
+            hipLaunchKernelGGL((k_fused<D, S, TL, M && std::is_same<C, float>::value, FAST.value, FOLD.value>), grid,
+                               dim3(TL::NT), 0, c->stream, a);
+        };
+        constexpr std::integral_constant<bool, !M && (D == 2 || fold_storage)> folding{};
+        constexpr std::integral_constant<bool, !M && D == 2> folding_general{};
+        if (fast_instance<M>(c)) launch(std::true_type(), folding);
+        else if (folding_general.value && !kfold(c)) launch(std::false_type(), std::false_type());
+        else launch(std::false_type(), folding_general);
         c->cur = nxt;
         c->pulled = 1;
         c->mc_pending = true;
@@ -773,7 +773,8 @@ template <int D, class S> struct Impl {
             hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
             hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &nb, k_fused<D, S, TL, M && std::is_same<C, float>::value, false>, TL::NT, 0) == hipSuccess &&
+                &nb, k_fused<D, S, TL, M && std::is_same<C, float>::value, false, !M && D == 2>, TL::NT, 0) ==
+                hipSuccess &&
             ncu > 0 && nb > 0;
         if (!known) (void)hipGetLastError();
         return known ? (long long)ncu * nb : 0;

@@ -76,7 +76,6 @@ template <class C, class T> struct FusedArgs {
     Phys<C> ph;
     RefPops ref;
     int ntx, nty, nseg;  // tiles along x, y; z segments
-    int fold;            // D2Q9 with the explicit EOS: 1 when the step completes its input moments itself
     int nsub;            // workgroups that share a tile's march through a segment
     int nlay;            // layers of Mc / IN: nz planes + 2 spill layers per segment (D = 3), 1 (D = 2)
     int chunk;           // tiles per XCD in the remapped order, 0: identity order
@@ -746,7 +745,9 @@ __global__ void __launch_bounds__(256, 2) k_eos_surrogate(Grid g, Phys<float> ph
 // workgroups was slower).
 template <class S, bool MLP> constexpr int fused_occupancy() { return sizeof(typename S::T) == 2 ? 2 : 1; }
 
-template <int D, class S, class TL, bool MLP, bool FAST>
+// FAST: full tiles, periodic x and y.  FOLD: the step completes its input moments
+// itself.
+template <int D, class S, class TL, bool MLP, bool FAST, bool FOLD>
 __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(FusedArgs<typename S::C, typename S::T> a) {
     using C = typename S::C;
     using T = typename S::T;
@@ -780,19 +781,19 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
         g.clampx = 0;
         g.clampy = 0;
     }
-    // FOLD (D2Q9, and on D3Q27 the full-tile periodic instances with 16-bit
-    // storage; the explicit EOS): the input side channel holds the previous
-    // step's tile-own partial sums -- complete only on the segment-end planes,
-    // which the fix-up completes -- and INi its inbound slots.  Every moment
-    // read is completed on load with the fix-up's terms, order and rounding (a
-    // perimeter cell adds its side, bottom/top and corner slot), so the step
-    // needs no pass over the tiles' perimeter cells.  The extra loads cost these
-    // instances no more than the pass they replace (D2Q9, FP32: 2048 x 1024 cells
-    // 104 us per step either way, 512 x 512 20.5 -> 19.0, 300 x 100, where the
-    // second launch was a third of the step, 12.1 -> 10.8); the FP32 instance on
-    // D3Q27, already at the register limit, ran 30 % slower with them and keeps
-    // the separate fix-up.
-    constexpr bool FOLD = !MLP && (D == 2 || (FAST && sizeof(T) == 2));
+    // FOLD (D2Q9 on tiles of at least 2 x 2 cells, and on D3Q27 the full-tile
+    // periodic instances with 16-bit storage; the explicit EOS): the input side
+    // channel holds the previous step's tile-own partial sums -- complete only on
+    // the segment-end planes, which the fix-up completes -- and INi its inbound
+    // slots.  Every moment read is completed on load with the fix-up's terms,
+    // order and rounding (a perimeter cell adds its side, bottom/top and corner
+    // slot), so the step needs no pass over the tiles' perimeter cells.  The extra
+    // loads cost these instances no more than the pass they replace (D2Q9, FP32:
+    // 2048 x 1024 cells 104 us per step either way, 512 x 512 20.5 -> 19.0, 300 x
+    // 100, where the second launch was a third of the step, 12.1 -> 10.8); the
+    // FP32 instance on D3Q27, already at the register limit, ran 30 % slower with
+    // them and keeps the separate fix-up.
+    static_assert(!FOLD || (!MLP && (D == 2 || (FAST && sizeof(T) == 2))), "instances that complete their moments");
     const long long N = g.N;
     const long long plane = (long long)g.nx * g.ny;
     const int tid = threadIdx.x;
@@ -974,7 +975,7 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
     // [z0 - 3, z1 + 5) meets no other segment's end plane
     const int zend_below = D == 3 ? zwrap(z0 - 1) : -1, zend_above = D == 3 ? zwrap(z1) : -1;
     auto is_end = [&](int p) {
-        if (D != 3) return a.fold == 0;  // completed by the fix-up: nothing to add
+        if (D != 3) return false;
         const int wp = zwrap(p);
         return wp == z0 || wp == z1 - 1 || wp == zend_below || wp == zend_above;
     };

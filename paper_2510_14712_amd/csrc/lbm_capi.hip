@@ -313,9 +313,14 @@ template <int D, class S> struct Impl {
         a.accw = 2 * ((c->p.nx + 63) / 64);
         a.inv_cv_d = 1.0 / (double)(float)c->p.cv;
         const dim3 grid((unsigned)(c->ntx * c->nty * c->nseg * c->nsub));
+        constexpr bool SUR = M && std::is_same<C, float>::value;
         auto launch = [&](auto FAST, auto FOLD) {
-            hipLaunchKernelGGL((k_fused<D, S, TL, M && std::is_same<C, float>::value, FAST.value, FOLD.value>), grid,
-                               dim3(TL::NT), 0, c->stream, a);
+            if (D == 3 && c->nsub > 1)
+                hipLaunchKernelGGL((k_fused<D, S, TL, SUR, FAST.value, FOLD.value, D == 3>), grid, dim3(TL::NT), 0,
+                                   c->stream, a);
+            else
+                hipLaunchKernelGGL((k_fused<D, S, TL, SUR, FAST.value, FOLD.value, false>), grid, dim3(TL::NT), 0,
+                                   c->stream, a);
         };
         constexpr std::integral_constant<bool, !M && (D == 2 || fold_storage)> folding{};
         constexpr std::integral_constant<bool, !M && D == 2> folding_general{};
@@ -764,8 +769,8 @@ template <int D, class S> struct Impl {
         c->zchunk = eos_chunk(c);
     }
     // Resident workgroups of the fused step: compute units x the kernel's
-    // occupancy (the instance the step launches); 0 if the device cannot be
-    // queried
+    // occupancy (of the general instance; on D3Q27 the LDS gives every instance
+    // of a storage form the same); 0 if the device cannot be queried
     template <bool M> static long long resident_groups() {
         using TL = TileOf<S, M>;
         int dev = 0, ncu = 0, nb = 0;
@@ -773,7 +778,7 @@ template <int D, class S> struct Impl {
             hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
             hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &nb, k_fused<D, S, TL, M && std::is_same<C, float>::value, false, !M && D == 2>, TL::NT, 0) ==
+                &nb, k_fused<D, S, TL, M && std::is_same<C, float>::value, false, !M && D == 2, false>, TL::NT, 0) ==
                 hipSuccess &&
             ncu > 0 && nb > 0;
         if (!known) (void)hipGetLastError();

@@ -76,7 +76,7 @@ template <class C, class T> struct FusedArgs {
     Phys<C> ph;
     RefPops ref;
     int ntx, nty, nseg;  // tiles along x, y; z segments
-    int nsub;            // workgroups that share a tile's march through a segment
+    int nsub;            // SHARED: workgroups that share a tile's march through a segment
     int nlay;            // layers of Mc / IN: nz planes + 2 spill layers per segment (D = 3), 1 (D = 2)
     int chunk;           // tiles per XCD in the remapped order, 0: identity order
     int pull;            // form of the input set: 0 arrived, 1 post-collision (read from x - c_i)
@@ -746,8 +746,8 @@ __global__ void __launch_bounds__(256, 2) k_eos_surrogate(Grid g, Phys<float> ph
 template <class S, bool MLP> constexpr int fused_occupancy() { return sizeof(typename S::T) == 2 ? 2 : 1; }
 
 // FAST: full tiles, periodic x and y.  FOLD: the step completes its input moments
-// itself.
-template <int D, class S, class TL, bool MLP, bool FAST, bool FOLD>
+// itself.  SHARED (D3Q27): a.nsub > 1 workgroups to a segment.
+template <int D, class S, class TL, bool MLP, bool FAST, bool FOLD, bool SHARED>
 __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(FusedArgs<typename S::C, typename S::T> a) {
     using C = typename S::C;
     using T = typename S::T;
@@ -793,6 +793,7 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
     // 100, where the second launch was a third of the step, 12.1 -> 10.8); the
     // FP32 instance on D3Q27, already at the register limit, ran 30 % slower with
     // them and keeps the separate fix-up.
+    static_assert(D == 3 || !SHARED, "shares of a march");
     static_assert(!FOLD || (!MLP && (D == 2 || (FAST && sizeof(T) == 2))), "instances that complete their moments");
     const long long N = g.N;
     const long long plane = (long long)g.nx * g.ny;
@@ -803,7 +804,8 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
     const int b = blockIdx.x;
     const int L = a.chunk ? (b & 7) * a.chunk + (b >> 3) : b;
     const int tx = L % a.ntx, ty = (L / a.ntx) % a.nty, part = L / (a.ntx * a.nty);
-    const int seg = part / a.nsub, nth = part - seg * a.nsub;
+    const int nsub = SHARED ? a.nsub : 1;
+    const int seg = part / nsub, nth = part - seg * nsub;
     const int x0 = tx * TX, y0 = ty * TY;
     const int w = FAST ? TX : min(TX, g.nx - x0), h = FAST ? TY : min(TY, g.ny - y0);
     const int nz = g.nz;
@@ -815,9 +817,11 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
     // sums of the planes next to it and not stored.  Every sum is then formed
     // from the same terms in the same order whatever the number of workgroups
     // (spill layers between them, as between segments, would change the order
-    // and with it the last bits).
-    const int zs = D == 3 ? z0 + seg_lo(nth, z1 - z0, a.nsub) : 0, ze = D == 3 ? z0 + seg_lo(nth + 1, z1 - z0, a.nsub) : 1;
-    const int za = max(zs - 1, z0), zb = min(ze + 1, z1);
+    // and with it the last bits).  An instance of its own: whose plane it is, asked
+    // at every store, took the marches that are not shared 1 % longer (512^3
+    // cells, BF16 + surrogate: 10.94 ms per step, without 10.84).
+    const int zs = SHARED ? z0 + seg_lo(nth, z1 - z0, nsub) : z0, ze = SHARED ? z0 + seg_lo(nth + 1, z1 - z0, nsub) : z1;
+    const int za = SHARED ? max(zs - 1, z0) : z0, zb = SHARED ? min(ze + 1, z1) : z1;
 
     // -- z-invariant per-thread set-up ---------------------------------------
     const int lx = tid % TX, ly = tid / TX;
@@ -1166,7 +1170,7 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
     // A plane that another workgroup writes goes to resources of no bytes, which
     // drop the stores.
     auto flush = [&](int p, int layer) {
-        const bool mine = (p >= zs && p < ze) || (p == z0 - 1 && zs == z0) || (p == z1 && ze == z1);
+        const bool mine = !SHARED || (p >= zs && p < ze) || (p == z0 - 1 && zs == z0) || (p == z1 && ze == z1);
         if (own) {
             const Rsrc mo = make_rsrc(a.Mco + (long long)layer * 5 * plane, mine ? mc_bytes : 0u);
             const bool plane_layer = D == 2 || layer < nz;
@@ -1454,7 +1458,7 @@ __global__ void __launch_bounds__(TL::NT, (fused_occupancy<S, MLP>())) k_fused(F
             constexpr unsigned PB = 2 * sizeof(T);  // bytes of an (f, g) pair
             const long long pb = 2 * (long long)(D == 3 ? z : 0) * Q * plane;
             // (a plane that another workgroup stores: a resource of no bytes)
-            const bool mine = z >= zs && z < ze;
+            const bool mine = !SHARED || (z >= zs && z < ze);
             const Rsrc ro = make_rsrc(a.fo + pb, mine ? (unsigned)((long long)Q * plane * PB) : 0u);
 #pragma unroll
             for (int i = 0; i < Q; i++) {

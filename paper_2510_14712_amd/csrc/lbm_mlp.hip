@@ -76,7 +76,7 @@ template <bool F32, int NT>
 __global__ void __launch_bounds__(256, 2) k_forward(const float *__restrict__ P, const float *__restrict__ norm,
                                                  const float *__restrict__ x, float *__restrict__ y, int B) {
     __shared__ __attribute__((aligned(16))) NetLds<3, F32> net;
-    net_to_lds(net, P, threadIdx.x, 256);
+    net_to_lds(net, P, (const uint16_t *)nullptr, threadIdx.x, 256);
     __syncthreads();
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     for (long long b0 = (blockIdx.x * 4ll + w) * (32 * NT); b0 < B; b0 += gridDim.x * 4ll * (32 * NT)) {
@@ -135,20 +135,26 @@ __global__ void __launch_bounds__(256, 2) k_forward_l1mfma(const float *__restri
 // A workgroup keeps the network in LDS and takes runs of 256-cell units as the
 // explicit read-back does (512^3 cells: 3.4 ms; with the parameters read from
 // global memory by every wavefront 9.4 ms for the fields, and 1.6 ms more to
-// export them).  Bound by the vector ALU.
+// export them).  Bound by the vector ALU; on small lattices by the latency of
+// putting the network into LDS, so the hidden weights come from their BF16 copy,
+// two 16-byte reads a lane, and blocks without cells end at once (Peng-Robinson
+// step of 129 x 30 cells: 25.8 us with the parameters read from global memory,
+// 29.5 with all of them converted by every block, so 18.9).
 enum { MLP_STEP, MLP_EXPORT, MLP_SUMS };
 template <int D, int MODE>
 __global__ void __launch_bounds__(BX, 2) k_cells_mlp(Grid g, Phys<float> ph, MomSrc<float> m, Fields<float> fl,
-                                                  const float *__restrict__ Pn, const float *__restrict__ norm,
+                                                  const float *__restrict__ Pn,
+                                                  const uint16_t *__restrict__ W2b, const float *__restrict__ norm,
                                                   float tol, unsigned long long *counters, ReadOut o) {
     __shared__ __attribute__((aligned(16))) NetLds<1, false> net;
-    net_to_lds(net, Pn, threadIdx.x, BX);
-    __syncthreads();
     double acc[RED_VALS] = {0, 0, 0, 0, 0, 0, 0};
     unsigned n_fb = 0, n_cell = 0, n_it = 0;
     long long u0, u1;
     unsigned per_plane;
     read_units(g, u0, u1, per_plane);
+    if (MODE != MLP_SUMS && u0 == u1) return;  // a small lattice leaves most blocks without work
+    if (u0 < u1) net_to_lds(net, Pn, W2b, threadIdx.x, BX);
+    __syncthreads();
     for (long long un = u0; un < u1; un++) {
         const int z = (int)((unsigned long long)un / per_plane);
         const unsigned p = (unsigned)(un - (long long)z * per_plane) * BX + threadIdx.x;
@@ -501,7 +507,7 @@ static Phys<float> make_phys_f32(const lbm_params &p) {
 template <int D, int MODE>
 static int launch_cells_mlp(lbm_ctx *c, const MomSrc<float> &m, const Fields<float> &fl, const ReadOut &o) {
     hipLaunchKernelGGL((mlp::k_cells_mlp<D, MODE>), dim3(READ_BLOCKS), dim3(BX), 0, c->stream, c->grid,
-                       make_phys_f32(c->p), m, fl, c->mlp_params, c->mlp_norm, (float)c->p.mlp_tol, c->mlp_counters, o);
+                       make_phys_f32(c->p), m, fl, c->mlp_params, c->mlp_w2b, c->mlp_norm, (float)c->p.mlp_tol, c->mlp_counters, o);
     return lbm_note(hipGetLastError());
 }
 template <int D, class C> int launch_fields_mlp(lbm_ctx *c, Fields<C> fl) {

@@ -70,8 +70,10 @@ template <int NOUT, bool F32> struct NetLds {
     float w1x[H], w1y[H], b1[H], b2[H], w3[NOUT][H], b3[4];
     typename std::conditional<F32, float, uint16_t>::type w2[H * W2LD];
 };
+// w2b: the hidden weights in BF16 where a copy of them is kept (16-byte aligned), else null
 template <int NOUT, bool F32>
-__device__ __forceinline__ void net_to_lds(NetLds<NOUT, F32> &n, const float *__restrict__ P, int tid, int nt) {
+__device__ __forceinline__ void net_to_lds(NetLds<NOUT, F32> &n, const float *__restrict__ P,
+                                           const uint16_t *__restrict__ w2b, int tid, int nt) {
     for (int k = tid; k < H; k += nt) {
         const int q = F32 ? 2 * (k & 31) + (k >> 5) : k;
         n.w1x[k] = P[OFF_W1 + 2 * q];
@@ -81,6 +83,13 @@ __device__ __forceinline__ void net_to_lds(NetLds<NOUT, F32> &n, const float *__
         for (int o = 0; o < NOUT; o++) n.w3[o][k] = P[OFF_W3 + o * H + k];
     }
     if (tid < NOUT) n.b3[tid] = P[OFF_B3 + tid];
+    if constexpr (!F32) {
+        if (w2b) {
+            for (int r = tid; r < H * H / 8; r += nt)
+                *(uint4 *)&n.w2[r / (H / 8) * n.W2LD + 8 * (r % (H / 8))] = ((const uint4 *)w2b)[r];
+            return;
+        }
+    }
     for (int r = tid; r < H * H; r += nt) {
         const int m = r / H, q = r % H;
         const float v = P[OFF_W2 + r];

@@ -59,8 +59,11 @@ __global__ void __launch_bounds__(64 * RED_VALS) k_reduce_final(int nblocks, con
 // population decode / encode between the storage form and FP64: the (f, g) pair
 // of a direction in one access, the caller's two arrays in whole lines.  Bound
 // by HBM (333 x 201 x 97 cells, FP16, 3.5 GB: read 1.27 ms and write 0.98 ms
-// with f and g apart, now 0.82 and 0.75; non-temporal stores of the read-out
-// 0.96).
+// with f and g apart, now 0.82 and 0.74; non-temporal stores of the read-out
+// 0.96).  The way in takes the non-temporal hint on both sides: the data come
+// from elsewhere and are read once.  With the hint on the loads alone, or on
+// neither, that write takes 0.87 and 0.73 ms, and after other traffic 128 x 9 x
+// 291 cells in BF16 41 and 63 us, with both 36 (f and g apart 61).
 template <int D, class S>
 __global__ void __launch_bounds__(BX) k_get_pops(Grid g, RefPops ref, const typename S::T *__restrict__ fi,
                                                  double *__restrict__ fo, double *__restrict__ go, SetForm form) {
@@ -90,9 +93,9 @@ __global__ void __launch_bounds__(BX) k_set_pops(Grid g, RefPops ref, const doub
     const long long xy = x + (long long)g.nx * y;
 #pragma unroll
     for (int i = 0; i < Q; i++)
-        store_pair(fo, pop_index<Q>(g, i, z, xy),
-                   S::enc((C)__builtin_nontemporal_load(&fi[i * g.N + c]), (C)ref.f[i]),
-                   S::enc((C)__builtin_nontemporal_load(&gi[i * g.N + c]), (C)ref.g[i]));
+        store_pair_nt(fo, pop_index<Q>(g, i, z, xy),
+                      S::enc((C)__builtin_nontemporal_load(&fi[i * g.N + c]), (C)ref.f[i]),
+                      S::enc((C)__builtin_nontemporal_load(&gi[i * g.N + c]), (C)ref.g[i]));
 }
 
 __global__ void k_codec_encode(int kind, const float *x, const float *ref, uint16_t *out, long long n) {

@@ -201,6 +201,11 @@ template <class T> __device__ __forceinline__ PopPair<T> load_pair(const T *p, l
 template <class T> __device__ __forceinline__ void store_pair(T *p, long long j, T f, T g) {
     *reinterpret_cast<PopPair<T> *>(p + j) = PopPair<T>{f, g};
 }
+// the same with the non-temporal hint
+template <class T> __device__ __forceinline__ void store_pair_nt(T *p, long long j, T f, T g) {
+    typedef T pair_t __attribute__((ext_vector_type(2)));
+    __builtin_nontemporal_store((pair_t){f, g}, reinterpret_cast<pair_t *>(p + j));
+}
 
 // Stored population sets come in two forms.  After initialisation (and after
 // lbm_set_populations) the set holds the arrived populations f_i(x) that the

@@ -144,6 +144,16 @@ static dim3 flat_grid(const lbm_ctx *c) {
     return dim3((unsigned)((plane + BX - 1) / BX), (unsigned)c->p.nz);
 }
 
+// compute units of the current device; if it cannot be queried, those of a whole MI355X
+static int compute_units() {
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0)
+        return ncu;
+    (void)hipGetLastError();
+    return 256;
+}
+
 static thread_local char g_last_error[256] = "";
 
 int lbm_note(hipError_t e) {
@@ -557,9 +567,14 @@ template <int D, class S> struct Impl {
     // step, by the shortest time per step of the model below (4 us per launch,
     // then a step's latency, which grows with the wavefronts per SIMD: fitted to
     // those and 512 x 4 2.1 and 1.8, 1000 x 4 2.2 and 1.9, 400 x 16 3.7 and 3.1,
-    // 800 x 32 FP32 5.1), where it is shorter than a step of the other path
-    // (fused 10 us, multi-kernel with x walls 20, on any of these).  Beyond 64
-    // (32) rows not even one step's region fits.
+    // 800 x 32 FP32 5.1; x walls, up to 1 us longer, take the same numbers).  It
+    // is taken below 8 us, with x walls below 16: a step of the other path takes
+    // 9 us and more there, 20 and more.  Up to 64 (32) rows, a choice: a region
+    // of one step would fit up to 85 (42), but from 64 (32) on most of it is
+    // halo and little is gained (us per step, other path against this one: FP32
+    // 64 x 64 10.6 and 6.2, 1000 x 64 11.5 and 9.8, 2048 x 64 13.5 and 11.0;
+    // FP64 1000 x 32 12.2 and 10.3; x walls 4096 x 32 FP32 23.4 and 15.0, FP64
+    // 28.9 and 18.6).
     static void block2d_plan(lbm_ctx *c) {
         c->b2_threads = 0;
         const bool wide = std::is_same<C, double>::value;
@@ -574,11 +589,12 @@ template <int D, class S> struct Impl {
         if ((long long)nx * ny <= cap) return plan(nx * ny, nx, 0, 1024);
         if (ny > cap / 16) return;
         const double launch = 4.0, base = wide ? 1.0 : 0.95, per = wide ? 0.65 : 0.45;
+        const int ncu = compute_units();
         double best = c->grid.wallx ? 16.0 : 8.0;
         for (int k = 1; k <= 16; k++)
             for (int own = 4; (own + 8 * k) * ny <= cap; own += 4) {
                 const int threads = (own + 8 * k) * ny;
-                const double rounds = std::ceil(((nx + own - 1) / own) / 256.0);
+                const double rounds = std::ceil(((nx + own - 1) / own) / (double)ncu);
                 const double t = rounds * (launch / k + base + per * ((threads + 255) / 256));
                 if (t >= best) continue;
                 best = t;

@@ -69,9 +69,9 @@ __device__ __forceinline__ f32x16 wave_tile64(const float *A, int ai, int ak, co
 
 // ---------------------------------------------------------------------------
 // Stand-alone forward.  A workgroup of four wavefronts puts the network into
-// LDS and takes blocks of 4 x 32 NT samples in turn; NT = 4 once every compute
-// unit has a workgroup with it, else 2 (more wavefronts, less work each).
-constexpr int FWD_BLOCKS = 1024;  // four workgroups per compute unit
+// LDS and takes blocks of 4 x 32 NT samples in turn; NT = 4 once each of 256
+// compute units has a workgroup with it, else 2 (more wavefronts, less work each).
+constexpr int FWD_BLOCKS = 1024;  // four workgroups for each of 256 compute units
 template <bool F32, int NT>
 __global__ void __launch_bounds__(256, 2) k_forward(const float *__restrict__ P, const float *__restrict__ norm,
                                                  const float *__restrict__ x, float *__restrict__ y, int B) {

@@ -341,7 +341,7 @@ struct StoreF16 {
 // which the host sums when it reads them.  A workgroup adds to the copy of its
 // number: adds to one address are served one after the other (about 10 ns
 // each), which at two adds per wavefront was most of the time that the
-// Peng-Robinson fields pass took (128^3 cells: 0.79 -> 0.12 ms).
+// Peng-Robinson fields pass took (128^3 cells: 0.80 -> 0.13 ms).
 constexpr int COUNTER_SLOTS = 256, COUNTER_STRIDE = 8;
 __device__ __forceinline__ unsigned long long *counter_slot(unsigned long long *counters) {
     const unsigned b = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);

@@ -1,6 +1,6 @@
 // Kernels of the non-ideal DDF lattice Boltzmann step (arXiv 2510.14712,
-// Section 3.2 and its flowchart).  Structure-of-arrays populations, x fastest;
-// one thread per cell, grid (ceil(nx / BX), ny, nz).
+// Section 3.2 and its flowchart).  One thread per cell, the cells of a plane in
+// a row: grid (ceil(nx ny / BX), nz), see flat_cell.
 //
 // One step is four launches:
 //   k_moments  rho, j = sum c_i f_i, G = sum g_i per cell           (eqs. def_h..)

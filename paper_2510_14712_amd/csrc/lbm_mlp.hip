@@ -365,7 +365,7 @@ __global__ void __launch_bounds__(256) k_train_partial(const float *__restrict__
 // and eight in flight), and lane p of the first wavefront adds the sums in order.
 // The last workgroup sums the block losses in FP64.  Bound by the latency of the
 // partials, which other XCDs have written (128 blocks: 17.6 us with four
-// wavefronts and one lane adding up the losses, now 3.9).
+// wavefronts and one lane adding up the losses, now 2.8).
 constexpr int SUM_WAVES = 16;
 __global__ void __launch_bounds__(64 * SUM_WAVES) k_sum_partials(const float *__restrict__ gpart,
                                                                  const float *__restrict__ lpart, int nblk, int B,

@@ -61,7 +61,7 @@ struct Net {
 // tile 112 instructions in the first layer, 32 (1 + NOUT) in the last), not the
 // parameter reads that a pass of one tile spends its time on (1,000,003 samples,
 // three outputs: 113 us with one wavefront per workgroup converting W2 for
-// itself, 29 us so).
+// itself, 25 us so).
 template <int NOUT, bool F32> struct NetLds {
     static constexpr int W2LD = F32 ? 68 : 72;  // padded rows: conflict-free 16-byte reads
     // first layer by input position: BF16 position k is neuron k; F32 position

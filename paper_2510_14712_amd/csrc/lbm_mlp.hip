@@ -249,7 +249,7 @@ __global__ void __launch_bounds__(256) k_train_partial(const float *__restrict__
                                                        const float *__restrict__ tn, int B, float *__restrict__ gpart,
                                                        float *__restrict__ lpart) {
     __shared__ float H1[64 * LD], H2[64 * LD], DZ[64 * LD], W2[64 * LD], X[64 * 2], DY[64 * 3];
-    __shared__ float Pr[3 * 64];  // squared residuals
+    __shared__ float Pr[3 * 64];  // residuals
     __shared__ float sB2[H], sW3[3 * H + 3];  // b2; w3, b3
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int mt = w >> 1, nt = w & 1;  // this wavefront's tile of each product
@@ -290,7 +290,7 @@ __global__ void __launch_bounds__(256) k_train_partial(const float *__restrict__
 #pragma unroll 16
         for (int n = 0; n < H; n++) s = fmaf(sW3[w * H + n], H2[lane * LD + n], s);
         const float r = s - target;
-        Pr[64 * w + lane] = r * r;
+        Pr[64 * w + lane] = r;
         DY[3 * lane + w] = scale * r;  // dL / dyhat
     }
     __syncthreads();
@@ -320,7 +320,8 @@ __global__ void __launch_bounds__(256) k_train_partial(const float *__restrict__
             for (int bb = 0; bb < 64; bb++) s += DY[3 * bb + lane];
             G[OFF_B3 + lane] = s;
         }
-        float sq = (Pr[lane] + Pr[64 + lane]) + Pr[128 + lane];
+        const float r0 = Pr[lane], r1 = Pr[64 + lane], r2 = Pr[128 + lane];
+        float sq = fmaf(r2, r2, fmaf(r1, r1, r0 * r0));
         for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
         if (lane == 0) lpart[blockIdx.x] = sq;
     }
@@ -362,7 +363,7 @@ __global__ void __launch_bounds__(256) k_train_partial(const float *__restrict__
 // Sum of the per-block partial gradients, in a fixed order: a workgroup takes
 // 64 parameters; its 16 wavefronts each sum a contiguous sixteenth of the blocks
 // for those parameters (a lane per parameter, loads coalesced across the lanes
-// and eight in flight), and lane p of the first wavefront adds the sums in order.
+// and eight in flight), and lane p of the first wavefront adds the sums in pairs.
 // The last workgroup sums the block losses in FP64.  Bound by the latency of the
 // partials, which other XCDs have written (128 blocks: 17.6 us with four
 // wavefronts and one lane adding up the losses, now 2.8).
@@ -390,10 +391,16 @@ __global__ void __launch_bounds__(64 * SUM_WAVES) k_sum_partials(const float *__
     part[w][lane] = s;
     __syncthreads();
     if (w == 0 && p < NP) {
-        float t = part[0][lane];
+        // in pairs: four roundings after those of a wavefront's run, where one
+        // after the other would be 15
+        float t[SUM_WAVES];
 #pragma unroll
-        for (int q = 1; q < SUM_WAVES; q++) t += part[q][lane];
-        grad[p] = t;
+        for (int q = 0; q < SUM_WAVES; q++) t[q] = part[q][lane];
+#pragma unroll
+        for (int n = SUM_WAVES / 2; n > 0; n /= 2)
+#pragma unroll
+            for (int q = 0; q < n; q++) t[q] += t[q + n];
+        grad[p] = t[0];
     }
 }
 

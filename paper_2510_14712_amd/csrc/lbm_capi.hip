@@ -327,12 +327,23 @@ template <int D, class S> struct Impl {
         a.inv_cv_d = 1.0 / (double)(float)c->p.cv;
         const dim3 grid((unsigned)(c->ntx * c->nty * c->nseg * c->nsub));
         constexpr bool SUR = M && std::is_same<C, float>::value;
+        // Three instances are scheduled better with the tests of the shared marches
+        // in them and are taken with them always (us per step of lattices that do
+        // not share, without and with): the general one of FP64 (100 x 75 x 60
+        // cells 132.6 and 130.6, 200 x 200 x 100 995 and 976), the full-tile ones
+        // of FP16 with the explicit EOS (256^3 1297 and 1255) and of FP32 with the
+        // surrogate (256^3 2197 and 2181).  The others without (full tiles, FP32
+        // 128^3 258 and 276, FP64 128^3 481 and 487; general, FP16 250 x 200 x 100
+        // 536 and 556).
         auto launch = [&](auto FAST, auto FOLD) {
-            if (D == 3 && c->nsub > 1)
+            constexpr bool always = D == 3 && (FAST.value ? (M ? std::is_same<S, StoreF32>::value
+                                                               : std::is_same<S, StoreF16>::value)
+                                                          : std::is_same<S, StoreF64>::value);
+            if (D == 3 && (always || c->nsub > 1))
                 hipLaunchKernelGGL((k_fused<D, S, TL, SUR, FAST.value, FOLD.value, D == 3>), grid, dim3(TL::NT), 0,
                                    c->stream, a);
             else
-                hipLaunchKernelGGL((k_fused<D, S, TL, SUR, FAST.value, FOLD.value, false>), grid, dim3(TL::NT), 0,
+                hipLaunchKernelGGL((k_fused<D, S, TL, SUR, FAST.value, FOLD.value, always>), grid, dim3(TL::NT), 0,
                                    c->stream, a);
         };
         constexpr std::integral_constant<bool, !M && (D == 2 || fold_storage)> folding{};
@@ -797,7 +808,7 @@ template <int D, class S> struct Impl {
             hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
             hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &nb, k_fused<D, S, TL, M && std::is_same<C, float>::value, false, !M && D == 2, false>, TL::NT, 0) ==
+                &nb, k_fused<D, S, TL, M && std::is_same<C, float>::value, false, !M && D == 2, D == 3>, TL::NT, 0) ==
                 hipSuccess &&
             ncu > 0 && nb > 0;
         if (!known) (void)hipGetLastError();
